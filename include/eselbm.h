@@ -134,6 +134,8 @@ typedef enum {
  *             sums (cells with all |x_i| below 0.02 in single precision and
  *             0.005 in double are evaluated through truncated power series
  *             of the same sums, accurate to the rounding of the type).
+ *             In the ELBM and ITERATE1 modes: cells beyond that bound, whose
+ *             condition takes a longer series or the logarithms themselves.
  *   n_newton  ELBM and ITERATE1 modes: Newton iterations summed over cells;
  *             with ES-BGK on (eselbm_set_prandtl), the quasi-equilibrium's
  *             Newton iterations.

@@ -10,6 +10,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace eselbm {
 
 // ---------------------------------------------------------------------------
@@ -440,6 +442,27 @@ struct SeriesCfgF16 {
     static constexpr double X = 0.01;
 };
 
+// The mirror modes' series (mirror_series): the sums are the mirror condition
+// itself, so the order is that of the arithmetic type whatever the storage.
+//   float,  X = 0.02,  K = 6: the remainder moves alpha by under 1.2e-8
+//           (|T_7| <= X^5 T_2, entering dH as (a^7/42 - a/6) T_7);
+//   double, X = 0.005, K = 8: under 6e-16 (X^7 T_2 times a^9/72 - a/8).
+// Beyond X, up to XE, the same sums are taken again to order KE in the type
+// of the exact path (mirror_extended):
+//   float,  XE = 0.08, KE = 10: 2.5e-9;   double, XE = 0.03, KE = 12: 1e-15.
+template <typename T>
+struct MirrorSeriesCfg;
+template <>
+struct MirrorSeriesCfg<float> {
+    static constexpr int K = 6, KE = 10;
+    static constexpr double X = 0.02, XE = 0.08;
+};
+template <>
+struct MirrorSeriesCfg<double> {
+    static constexpr int K = 8, KE = 12;
+    static constexpr double X = 0.005, XE = 0.03;
+};
+
 template <typename T>
 __device__ inline T fmin_(T a, T b) { return __builtin_fmin(a, b); }
 template <>
@@ -619,27 +642,14 @@ __device__ inline T log1p_series(T y)
     return s * y;
 }
 
-// alpha from the mirror condition in the arithmetic type A: the converged
-// root (FULL, the ELBM mode) or one Newton step from alpha_Lower (the
-// Iterate1 mode).  Returns alpha_Lower, with info.fallback set, where the
-// result is not a mirror path length in (1, a*): no root (the mirror leaves
-// the polytope) or a step outside the interval.
-template <int D, typename T, typename A, bool SH, bool FULL, typename P>
-__device__ __attribute__((always_inline)) inline A mirror_alpha(const P &p, const T (&d)[Lat<D>::Q], A aL, A xmin, CellInfo &info)
+// Newton's iteration on the mirror condition from alpha_Lower: the converged
+// root (FULL, the ELBM mode) or one step (the Iterate1 mode).  dH(a, F, Fp)
+// returns dH and its derivative at a.  Returns alpha_Lower, with
+// info.fallback set, where the result is not a mirror path length in (1, a*):
+// no root (the mirror leaves the polytope) or a step outside the interval.
+template <typename A, bool FULL, typename DH>
+__device__ __attribute__((always_inline)) inline A mirror_newton(DH dH, A aL, A xmin, CellInfo &info)
 {
-    constexpr int Q = Lat<D>::Q;
-    auto xof = [&](int i) { return A(d[i]) * rcp_(A(gval<D, T, SH>(i, p))); };
-    A S = A(0), xa = A(0);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) xa = fmax_(xa, abs_(xof(i)));
-    // S by the series of log(1 + x) where every x of the wave is in its range
-    if (__ballot(!(xa < A(MirrorCfg<A>::Y))) == 0ull) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) S = fma_(A(d[i]), log1p_series(xof(i)), S);
-    } else {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) S = fma_(A(d[i]), log1p_(xof(i)), S);
-    }
     const A astar = A(-1) * rcp_(xmin);
     A lo = A(1), hi = astar;
     const bool start_ok = aL > lo && aL < hi;
@@ -648,27 +658,8 @@ __device__ __attribute__((always_inline)) inline A mirror_alpha(const P &p, cons
     int it = 0;
     if (!fell) {
         for (; it < (FULL ? MirrorCfg<A>::maxit : 1); ++it) {
-            A F = -a * S, Fp = -S;
-            // every y = a x_i of every lane of the wave within the series
-            // range: phi and log(1 + y) both by their series (a wave-uniform
-            // choice; no logarithm evaluated)
-            if (__ballot(!(a * xa < A(MirrorCfg<A>::Y))) == 0ull) {
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    const A y = a * xof(i);
-                    const A l = log1p_series(y);
-                    F = fma_(A(gval<D, T, SH>(i, p)), phi_series(y), F);
-                    Fp = fma_(A(d[i]), l, Fp);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    const A y = a * xof(i);
-                    const A l = log1p_(y);
-                    F = fma_(A(gval<D, T, SH>(i, p)), phi_(y, l), F);
-                    Fp = fma_(A(d[i]), l, Fp);
-                }
-            }
+            A F, Fp;
+            dH(a, F, Fp);
             if (F > A(0)) hi = a; else lo = a;
             A an = a - F * rcp_(Fp);
             // a step onto the bracket's end is the root itself (F = 0)
@@ -690,16 +681,164 @@ __device__ __attribute__((always_inline)) inline A mirror_alpha(const P &p, cons
     return fell ? aL : a;
 }
 
+// The mirror condition from the power moments T_k = <g, x^k> that the path
+// length's series path has at hand (|x| below the bound of MirrorSeriesCfg):
+//   dH(a) = sum_k (-1)^k T_k (a^k / (k (k-1)) - a / (k-1)) = a G(a),
+//   G(a)  = sum_k (-1)^k T_k / (k-1) (a^(k-1) / k - 1),
+// so a Newton step costs K terms instead of a pass over the Q populations.
+// The leading term of G, T_2 (a/2 - 1), carries no cancellation, unlike the
+// difference of two sums.  With this, mirror_extended and the row-wise passes
+// of mirror_alpha the modes run at the plain step's registers and occupancy
+// (F32 D3Q27: 256 -> 121 VGPRs, two -> four waves per SIMD).  150x150x120,
+// per step, in a developed near-inviscid vortex: ELBM 307 -> 204 us (F32),
+// 591 -> 338 us (FP64); one Newton step 264 -> 189 us (F32).
+template <typename T, bool FULL, int K>
+__device__ __attribute__((always_inline)) inline T mirror_series(const T *Tm, T aL, T xmin, CellInfo &info)
+{
+    return mirror_newton<T, FULL>(
+        [&](T a, T &F, T &Fp) {
+            // Horner in a of G + S' and of its derivative, S' = sum (-1)^k T_k / (k-1)
+            T p = T((K % 2 ? -1.0 : 1.0) / (K * (K - 1.0))) * Tm[K], dp = T(0), s = T((K % 2 ? -1.0 : 1.0) / (K - 1.0)) * Tm[K];
+#pragma unroll
+            for (int k = K - 1; k >= 3; --k) {
+                dp = fma_(dp, a, p);
+                p = fma_(p, a, T((k % 2 ? -1.0 : 1.0) / (k * (k - 1.0))) * Tm[k]);
+                s = fma_(T((k % 2 ? -1.0 : 1.0) / (k - 1.0)), Tm[k], s);
+            }
+            // p = sum_{k>=3} (-1)^k T_k a^(k-3) / (k (k-1)), dp = dp/da:
+            // G = T_2 (a/2 - 1) + (a^2 p - s), G' = T_2/2 + a (2 p + a dp)
+            const T G = fma_(Tm[2], fma_(T(0.5), a, T(-1)), fma_(a * a, p, -s));
+            const T Gp = fma_(a, fma_(a, dp, p + p), T(0.5) * Tm[2]);
+            F = a * G;
+            Fp = fma_(a, Gp, G);
+        },
+        aL, xmin, info);
+}
+
+// alpha from the mirror condition beyond the common series' bound: one pass
+// forms the power moments to order KE in A (about 30 issue slots a
+// population; the passes of alpha_exact and mirror_alpha over rationals and
+// logarithms take about 190), for the flows whose departures are moderate.
+template <int D, typename T, typename A, bool SH, bool FULL, typename P>
+__device__ __attribute__((always_inline)) inline A mirror_extended(const P &p, const T (&d)[Lat<D>::Q], A &xmin, CellInfo &info)
+{
+    constexpr int Q = Lat<D>::Q, K = MirrorSeriesCfg<T>::KE;
+    A Tm[K + 1], N3 = A(0);
+    xmin = A(0);
+#pragma unroll
+    for (int k = 0; k <= K; ++k) Tm[k] = A(0);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        // one population at a time, as in alpha_exact
+        T g0 = gval<D, T, SH>(i, p), d0 = d[i];
+        asm volatile("" : "+v"(g0), "+v"(d0));
+        const A di = A(d0), x = di * rcp_(A(g0));
+        xmin = fmin_(xmin, x);
+        const A xn = fmin_(x, A(0));
+        N3 = fma_(di * xn, xn, N3);
+        A xk = x;
+#pragma unroll
+        for (int k = 2; k <= K; ++k) {
+            Tm[k] = fma_(di, xk, Tm[k]);
+            if (k < K) xk *= x;
+        }
+#pragma unroll
+        for (int k = 2; k <= K; ++k) asm volatile("" : "+v"(Tm[k]));
+        asm volatile("" : "+v"(N3), "+v"(xmin));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // C1 = sum_k (-1/2)^(k-2) T_k
+    A C1 = Tm[K];
+#pragma unroll
+    for (int k = K - 1; k >= 2; --k) C1 = fma_(C1, A(-0.5), Tm[k]);
+    const A aL = conj_root(A(0.5) * N3, A(0.5) * Tm[2], C1);
+    return mirror_series<A, FULL, K>(Tm, aL, xmin, info);
+}
+
+// alpha from the mirror condition in the arithmetic type A, by passes over
+// the populations: the cells beyond the bounds of both series.
+template <int D, typename T, typename A, bool SH, bool FULL, typename P>
+__device__ __attribute__((always_inline)) inline A mirror_alpha(const P &p, const T (&d)[Lat<D>::Q], A aL, A xmin, CellInfo &info)
+{
+    constexpr int Q = Lat<D>::Q;
+    // one x-row of three populations at a time: read through an empty asm,
+    // their terms added before the next row is read; otherwise the terms of
+    // many populations (a logarithm each) are live at once and spill, and one
+    // at a time their dependent chains would be exposed
+    auto read = [&](int i, A &g, A &di) {
+        T g0 = gval<D, T, SH>(i, p), d0 = d[i];
+        asm volatile("" : "+v"(g0), "+v"(d0));
+        g = A(g0);
+        di = A(d0);
+        return di * rcp_(g);
+    };
+    A S = A(0), xa = A(0), g, di;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        xa = fmax_(xa, abs_(read(i, g, di)));
+        if (i % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+    }
+    // S by the series of log(1 + x) where every x of the wave is in its range
+    auto sum_S = [&](auto log_of) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const A x = read(i, g, di);
+            S = fma_(di, log_of(x), S);
+            if (i % 3 == 2) {
+                asm volatile("" : "+v"(S));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    if (__ballot(!(xa < A(MirrorCfg<A>::Y))) == 0ull) sum_S([](A x) { return log1p_series(x); });
+    else sum_S([](A x) { return log1p_(x); });
+    return mirror_newton<A, FULL>(
+        [&](A a, A &F, A &Fp) {
+            F = -a * S;
+            Fp = -S;
+            auto sum_F = [&](auto log_phi) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const A y = a * read(i, g, di);
+                    A l, ph;
+                    log_phi(y, l, ph);
+                    F = fma_(g, ph, F);
+                    Fp = fma_(di, l, Fp);
+                    if (i % 3 == 2) {
+                        asm volatile("" : "+v"(F), "+v"(Fp));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            };
+            // every y = a x_i of every lane of the wave within the series
+            // range: phi and log(1 + y) both by their series (a wave-uniform
+            // choice; no logarithm evaluated)
+            if (__ballot(!(a * xa < A(MirrorCfg<A>::Y))) == 0ull) {
+                sum_F([](A y, A &l, A &ph) {
+                    l = log1p_series(y);
+                    ph = phi_series(y);
+                });
+            } else {
+                sum_F([](A y, A &l, A &ph) {
+                    l = log1p_(y);
+                    ph = phi_(y, l);
+                });
+            }
+        },
+        aL, xmin, info);
+}
+
 // Path length of one cell from the populations (p) and d = feq - g.  The
 // gate and the series run in T; the exact path, with its guard, in A (a
 // cell whose x reach beyond the series bound has populations far from the
 // equilibrium, and the update multiplies an error of alpha by x relative to
 // g: double sums there keep that product below the storage rounding).
-template <int D, typename T, typename A, int MODE, bool SH, typename SC = SeriesCfg<T>, typename P>
+template <int D, typename T, typename A, int MODE, bool SH, typename SCS = SeriesCfg<T>, typename P>
 __device__ __attribute__((always_inline)) inline T path_length(const P &p, const T (&d)[Lat<D>::Q], double beta64, CellInfo &info)
 {
     constexpr int Q = Lat<D>::Q;
     const T beta = T(beta64);
+    using SC = typename std::conditional<is_mirror_mode(MODE), MirrorSeriesCfg<T>, SCS>::type;
     constexpr int K = SC::K;
     // moment arrays reach index 6 at least (a takes N_3..N_6; those beyond K
     // stay zero)
@@ -709,7 +848,7 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
     info.exact = 0;
     info.iters = 0;
     info.fallback = 0;
-    if (MODE == MODE_BGK || MODE == MODE_LBGK) return T(2);
+    if constexpr (MODE == MODE_BGK || MODE == MODE_LBGK) return T(2);
     // the mirror modes start from alpha_Lower
     constexpr int CMODE = is_mirror_mode(MODE) ? MODE_LOWER : MODE;
 
@@ -750,9 +889,9 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
         alpha = T(2);  // near-equilibrium gate (App. D)
         info.gated = 1;
     } else if (xabs < T(SC::X)) {
-        // series of 2x^2/(2+x), x^2 N3/P3 and R(y); coefficients for x^2..x^8
-        // and y^0..y^5 (exact rationals)
-        constexpr double c1k[7] = {1.0, -0.5, 0.25, -0.125, 0.0625, -0.03125, 0.015625};
+        // series of 2x^2/(2+x), x^2 N3/P3 and R(y); coefficients for x^2..x^9
+        // (the first), x^2..x^8 and y^0..y^5 (exact rationals)
+        constexpr double c1k[8] = {1.0, -0.5, 0.25, -0.125, 0.0625, -0.03125, 0.015625, -0.0078125};
         constexpr double ck[7] = {1.0, -0.5, 1.0 / 3.0, -0.25, 0.2, -1.0 / 6.0, 57.0 / 400.0};
         constexpr double rk[6] = {1.25, -0.625, 0.375, -0.25, 45.0 / 256.0, -65.0 / 512.0};
         const T b1 = T(0.5) * Tm[2];
@@ -760,12 +899,13 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
 #pragma unroll
         for (int k = 2; k <= K; ++k) {
             C1 += T(c1k[k - 2]) * Tm[k];
-            C += T(ck[k - 2]) * Tm[k];
+            if constexpr (CMODE != MODE_LOWER) C += T(ck[k - 2]) * Tm[k];
         }
         const T aL = conj_root(T(0.5) * Nm[3], b1, C1);
-        if (CMODE == MODE_LOWER) {
+        if constexpr (is_mirror_mode(MODE)) {
+            alpha = mirror_series<T, MODE == MODE_ELBM, K>(Tm, aL, xmin, info);
+        } else if constexpr (CMODE == MODE_LOWER) {
             alpha = aL;
-            if (is_mirror_mode(MODE)) alpha = mirror_alpha<D, T, T, SH, MODE == MODE_ELBM>(p, d, aL, xmin, info);
         } else {
             // Bp = sum_m r_m aL^m P_{3+m}, P_k = Tm[k] - Nm[k], by Horner
             T Bp = T(rk[K - 3]) * (Tm[K] - Nm[K]);
@@ -776,9 +916,17 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
     } else {
         info.exact = 1;
         // alpha and its positivity guard (App. D) in A
-        A xm;
-        A al = alpha_exact<D, T, A, CMODE, SH>(p, d, A(beta64), xm);
-        if (is_mirror_mode(MODE)) al = mirror_alpha<D, T, A, SH, MODE == MODE_ELBM>(p, d, al, xm, info);
+        A xm, al;
+        if constexpr (is_mirror_mode(MODE)) {
+            if (xabs < T(SC::XE)) {
+                al = mirror_extended<D, T, A, SH, MODE == MODE_ELBM>(p, d, xm, info);
+            } else {
+                al = alpha_exact<D, T, A, CMODE, SH>(p, d, A(beta64), xm);
+                al = mirror_alpha<D, T, A, SH, MODE == MODE_ELBM>(p, d, al, xm, info);
+            }
+        } else {
+            al = alpha_exact<D, T, A, CMODE, SH>(p, d, A(beta64), xm);
+        }
         if (xm < A(0)) {
             const A amax = A(-1) * rcp_(A(beta64) * xm);
             if (al > amax) {

@@ -206,7 +206,7 @@ __device__ inline const auto &pick(const X &a, const Y &b)
 template <int D, typename S, int MODE, bool WALL, bool QE, int AA>
 constexpr int stash_pops()
 {
-    return (D == 3 && !WALL && !QE && AA == 0 && (MODE == MODE_HIGHER || MODE == MODE_LOWER)) ? StepPolicy<S>::stash : 0;
+    return (D == 3 && !WALL && !QE && AA == 0 && (MODE == MODE_HIGHER || MODE == MODE_LOWER || is_mirror_mode(MODE))) ? StepPolicy<S>::stash : 0;
 }
 
 // d = feq - g of one cell, with moments and equilibrium in EQ, rounded to T,
@@ -243,19 +243,13 @@ __device__ inline void form_deviation(Dev dev, EQ drho, const EQ (&j)[3], T (&d)
     if constexpr (CONSERVE) conserve_moments<D, T>(d);
 }
 
-// The mirror-condition modes iterate over Q logarithms per Newton step:
-// they are ALU-bound, and their loop needs the registers of two waves per
-// SIMD.
-template <typename S, int MODE>
-constexpr int step_waves() { return is_mirror_mode(MODE) ? 2 : StepPolicy<S>::waves; }
-
 // The ES-BGK quasi-equilibrium solve holds a K x K factor, its moments and
 // the Newton state besides the two Q-arrays: two waves per SIMD for D2Q9 in
 // single precision, one for D3Q27 (K = 10) or where the solve runs in double.
 template <int D, typename S, int MODE, bool QE>
 constexpr int step_waves_qe()
 {
-    return QE ? ((StepPolicy<S>::eq_f64 || D == 3) ? 1 : 2) : step_waves<S, MODE>();
+    return QE ? ((StepPolicy<S>::eq_f64 || D == 3) ? 1 : 2) : StepPolicy<S>::waves;
 }
 
 // The walled step runs the periodic pull in all but the boundary layers, so
@@ -272,7 +266,7 @@ template <int D, typename S, int MODE, bool WALL, bool QE, bool FORCE, int AA>
 constexpr int step_waves_k()
 {
     return stash_pops<D, S, MODE, WALL, QE, AA>() > 0 ? StepPolicy<S>::stash_waves
-           : WALL ? (is_mirror_mode(MODE) ? 1 : (step_waves_qe<D, S, MODE, QE>() > 3 ? 3 : step_waves_qe<D, S, MODE, QE>()))
+           : WALL ? (step_waves_qe<D, S, MODE, QE>() > 3 ? 3 : step_waves_qe<D, S, MODE, QE>())
                   : (FORCE && step_waves_qe<D, S, MODE, QE>() > 3 ? 3 : step_waves_qe<D, S, MODE, QE>());
 }
 

@@ -18,7 +18,7 @@ import torch
 import oracle
 from oracle import torch_ref as TR
 from paper_2203_12946_amd import workloads as W
-from tests._states import mixed_mirror_lattice
+from tests._states import mixed_mirror_lattice, unstream
 
 pytestmark = pytest.mark.gpu
 
@@ -226,3 +226,34 @@ def test_adjoint_rejects_mirror_modes(es):
     with pytest.raises(es.EselbmError) as ei:
         s.adjoint_step(f, lam, out, 1e-2)
     assert ei.value.status == es.E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("mode", ["elbm", "iterate1"])
+@pytest.mark.parametrize("D,shape", [(2, (9, 70)), (3, (3, 4, 65))])
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f32s", "f16s"])
+def test_mirror_series_bands(es, D, shape, mode, dtype):
+    """Cells whose max|x| lies just inside and just beyond each bound of the
+    two power series (double 0.005 and 0.03, single 0.02 and 0.08): per-cell
+    alpha against the oracle, at the tolerances of the module (FP16 storage
+    as single precision: its arithmetic is single)."""
+    rng = np.random.default_rng(5 + D)
+    u = 0.03 * rng.standard_normal((D,) + shape)
+    g = oracle.init_equilibrium(1 + 0.01 * rng.standard_normal(shape), u)
+    amp = rng.choice([2e-3, 4.6e-3, 5.4e-3, 0.018, 0.022, 0.028, 0.032, 0.075, 0.085], size=shape)
+    f0 = _rounded(unstream(g * (1 + amp * rng.choice([-1.0, 1.0], g.shape) * rng.uniform(0.8, 1.0, g.shape))), dtype)
+    if dtype == "f16s":
+        w = oracle.lattice(D)[1].reshape((-1,) + (1,) * D)
+        f0 = w + (f0 - w).astype(np.float16).astype(np.float64)
+    _, ra, _ = oracle.step(f0, 1, 2e-3, mode=mode, want_alpha=True)
+    s = es.Solver("D2Q9" if D == 2 else "D3Q27", shape, dtype=dtype, mode=mode)
+    alpha = torch.empty(shape, dtype=s.compute_dtype, device="cuda")
+    s.set_alpha_field(alpha)
+    s.set_stats(True)
+    up = f0 - oracle.lattice(D)[1].reshape((-1,) + (1,) * D) if dtype == "f16s" else f0
+    fa = torch.from_numpy(up).to(s.storage_dtype).cuda() if dtype == "f16s" else _upload(s, f0, dtype)
+    s.step(fa, s.empty_state(), 1, 2e-3)
+    st = s.stats()
+    err = np.abs(alpha.double().cpu().numpy() - ra)
+    _log(f"[bands {mode} D{D} {dtype}] max|dalpha|={err.max():.2e}, exact {st['n_exact']}, gated {st['n_gated']}")
+    assert 0 < st["n_exact"] < err.size
+    assert err.max() <= (1e-9 if dtype == "f64" else 1e-5)
