@@ -442,25 +442,64 @@ struct SeriesCfgF16 {
     static constexpr double X = 0.01;
 };
 
+// Beyond X, up to X below, the same sums are taken again to order K in the
+// type of the exact path (alpha_extended), from one pass instead of the two
+// of the exact rationals.  The remainder of R sets the bound; it moves alpha by
+//   FP64:            X = 0.05, K = 14: under 5e-16, and the update by 3e-17 of g;
+//   4- and 2-byte:   X = 0.1,  K = 10: under 2e-8, and the update by 2e-9 of g.
+template <typename T>
+struct ExtendedCfg;
+template <>
+struct ExtendedCfg<float> {
+    static constexpr int K = 10;
+    static constexpr double X = 0.1;
+};
+template <>
+struct ExtendedCfg<double> {
+    static constexpr int K = 14;
+    static constexpr double X = 0.05;
+};
+// Taylor coefficients (exact rationals) of 2/(2+x) and of the fraction of c
+// over x^2, for x^0.., and of R(y)
+constexpr double kC1[13] = {1.0, -0.5, 0.25, -1.0 / 8.0, 1.0 / 16.0, -1.0 / 32.0, 1.0 / 64.0, -1.0 / 128.0,
+                            1.0 / 256.0, -1.0 / 512.0, 1.0 / 1024.0, -1.0 / 2048.0, 1.0 / 4096.0};
+constexpr double kC[13] = {1.0, -0.5, 1.0 / 3.0, -0.25, 1.0 / 5.0, -1.0 / 6.0, 57.0 / 400.0, -99.0 / 800.0,
+                           2603.0 / 24000.0, -1529.0 / 16000.0, 13513.0 / 160000.0, -71779.0 / 960000.0,
+                           212029.0 / 3200000.0};
+constexpr double kR[12] = {1.25, -5.0 / 8.0, 3.0 / 8.0, -0.25, 45.0 / 256.0, -65.0 / 512.0, 381.0 / 4096.0,
+                           -563.0 / 8192.0, 3345.0 / 65536.0, -4985.0 / 131072.0, 29781.0 / 1048576.0,
+                           -44543.0 / 2097152.0};
+
 // The mirror modes' series (mirror_series): the sums are the mirror condition
 // itself, so the order is that of the arithmetic type whatever the storage.
 //   float,  X = 0.02,  K = 6: the remainder moves alpha by under 1.2e-8
 //           (|T_7| <= X^5 T_2, entering dH as (a^7/42 - a/6) T_7);
 //   double, X = 0.005, K = 8: under 6e-16 (X^7 T_2 times a^9/72 - a/8).
-// Beyond X, up to XE, the same sums are taken again to order KE in the type
-// of the exact path (mirror_extended):
-//   float,  XE = 0.08, KE = 10: 2.5e-9;   double, XE = 0.03, KE = 12: 1e-15.
+// Beyond X, the extended moments:
+//   float,  X = 0.08, K = 10: 2.5e-9;   double, X = 0.03, K = 12: 1e-15.
 template <typename T>
 struct MirrorSeriesCfg;
 template <>
 struct MirrorSeriesCfg<float> {
-    static constexpr int K = 6, KE = 10;
-    static constexpr double X = 0.02, XE = 0.08;
+    static constexpr int K = 6;
+    static constexpr double X = 0.02;
 };
 template <>
 struct MirrorSeriesCfg<double> {
-    static constexpr int K = 8, KE = 12;
-    static constexpr double X = 0.005, XE = 0.03;
+    static constexpr int K = 8;
+    static constexpr double X = 0.005;
+};
+template <typename T>
+struct MirrorExtendedCfg;
+template <>
+struct MirrorExtendedCfg<float> {
+    static constexpr int K = 10;
+    static constexpr double X = 0.08;
+};
+template <>
+struct MirrorExtendedCfg<double> {
+    static constexpr int K = 12;
+    static constexpr double X = 0.03;
 };
 
 template <typename T>
@@ -510,6 +549,19 @@ struct PopAccess {
     __device__ T operator[](int i) const { return i < NS ? col[i * kStashStride] : tail[i - NS]; }
 };
 
+// Population i and d_i as fresh values: the empty asm keeps the compiler from
+// forming what follows from them ahead of this point, or reusing what an
+// earlier pass formed (the stored value is what it hides: a shifted format's
+// g = w + p_i would otherwise be kept from the first pass, in scratch).
+template <int D, typename T, bool SH, typename P>
+__device__ inline void fresh(int i, const P &p, const T (&d)[Lat<D>::Q], T &g, T &di)
+{
+    T v = T(p[i]);
+    di = d[i];
+    asm volatile("" : "+v"(v), "+v"(di));
+    g = SH ? T(Lat<D>::w(i)) + v : v;
+}
+
 // Exact rational sums in the arithmetic type A from the populations (p) and
 // d = feq - g in T; x_i = d_i / g_i is formed on the fly in A (twice: for
 // the Omega+- sums and for the Omega+ fractions of b), so d stays intact and
@@ -523,13 +575,12 @@ __device__ __attribute__((always_inline)) inline A alpha_exact(const P &p, const
     xmin = A(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        // the population is read here (the empty asm keeps the compiler from
-        // forming it, or its x, ahead of this iteration), and its terms are
-        // added to the sums before the next population's are formed (the
-        // empty asm at the end pins the sums there): otherwise the terms of
-        // many populations stay live at once and spill to scratch
-        T gi0 = gval<D, T, SH>(i, p), di0 = d[i];
-        asm volatile("" : "+v"(gi0), "+v"(di0));
+        // the population is read here, and its terms are added to the sums
+        // before the next population's are formed (the empty asm at the end
+        // pins the sums there): otherwise the terms of many populations stay
+        // live at once and spill to scratch
+        T gi0, di0;
+        fresh<D, T, SH>(i, p, d, gi0, di0);
         const A di = A(di0);
         const A xi = di * rcp_(A(gi0));
         xmin = fmin_(xmin, xi);
@@ -559,19 +610,88 @@ __device__ __attribute__((always_inline)) inline A alpha_exact(const P &p, const
     A Bp = A(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        // x again, from d and g (the empty asm keeps the compiler from
-        // holding the first loop's Q values of x live instead)
-        T gi = gval<D, T, SH>(i, p), di = d[i];
-        asm volatile("" : "+v"(gi), "+v"(di));
+        // x again, from d and g (not the first loop's Q values of x, which
+        // would be held live); the sum pinned as above
+        T gi, di;
+        fresh<D, T, SH>(i, p, d, gi, di);
         const A dp = fmax_(A(di), A(0));
         const A xp = dp * rcp_(A(gi));  // x on Omega+, else 0
         const A y = aL * xp;
         const A num = A(80) + y * (A(80) + A(19) * y);
         const A den = A(64) + y * (A(96) + y * (A(44) + A(6) * y));
         Bp += dp * xp * xp * num * rcp_(den);  // g x^3 R(aL x) on Omega+, else 0
+        asm volatile("" : "+v"(Bp));
         __builtin_amdgcn_sched_barrier(0);
     }
     return higher_from_coeffs(aL, b1, Bp, C, M3, M4, M5, M6, beta);
+}
+
+// alpha_Lower, and alpha_Higher from it, through the Taylor series of the
+// rational sums: Tm[k] = <g, x^k>, Nm[k] = <g, x^k>_- for k <= K (Nm to 6 at
+// least, zero beyond K; Nm[3] alone for alpha_Lower).
+template <typename T, int K>
+__device__ inline T lower_series(const T *Tm, const T *Nm)
+{
+    T C1 = T(0);
+#pragma unroll
+    for (int k = 2; k <= K; ++k) C1 += T(kC1[k - 2]) * Tm[k];
+    return conj_root(T(0.5) * Nm[3], T(0.5) * Tm[2], C1);
+}
+template <typename T, int K>
+__device__ inline T higher_series(const T *Tm, const T *Nm, T beta)
+{
+    const T aL = lower_series<T, K>(Tm, Nm);
+    T C = T(0);
+#pragma unroll
+    for (int k = 2; k <= K; ++k) C += T(kC[k - 2]) * Tm[k];
+    // Bp = sum_m r_m aL^m P_{3+m}, P_k = Tm[k] - Nm[k], by Horner
+    T Bp = T(kR[K - 3]) * (Tm[K] - Nm[K]);
+#pragma unroll
+    for (int k = K - 1; k >= 3; --k) Bp = Bp * aL + T(kR[k - 3]) * (Tm[k] - Nm[k]);
+    return higher_from_coeffs(aL, T(0.5) * Tm[2], Bp, C, Nm[3], Nm[4], Nm[5], Nm[6], beta);
+}
+
+// The power moments of a cell beyond the common series' bound in the type of
+// the exact path, Tm to order K and Nm to order KN, with x_min: one pass, an
+// x-row of three populations at a time (read through an empty asm, their
+// terms added before the next row is read).  About 45 issue slots a
+// population, a third fewer than the exact rationals' two passes, whose
+// reciprocals also follow one another in a serial chain.  Developed
+// near-inviscid 128^3 vortex (88% of the cells beyond 0.005, 2% beyond 0.05),
+// per step: FP64 447 -> 273 us, F32 163 -> 127 us, F32-shifted 176 -> 141 us
+// (with the second pass of alpha_exact kept from spilling, which alone gave
+// FP64 323 us).
+template <int D, typename T, typename A, bool SH, int K, int KN, typename P>
+__device__ __attribute__((always_inline)) inline void extended_moments(const P &p, const T (&d)[Lat<D>::Q], A *Tm, A *Nm, A &xmin)
+{
+    constexpr int Q = Lat<D>::Q;
+    xmin = A(0);
+#pragma unroll
+    for (int k = 0; k <= K; ++k) Tm[k] = Nm[k] = A(0);
+#pragma unroll
+    for (int r = 0; r < Q; r += 3) {
+#pragma unroll
+        for (int i = r; i < r + 3; ++i) {
+            T g0, d0;
+            fresh<D, T, SH>(i, p, d, g0, d0);
+            const A di = A(d0), x = di * rcp_(A(g0));
+            xmin = fmin_(xmin, x);
+            const A dn = fmin_(di, A(0));
+            A xk = x;
+#pragma unroll
+            for (int k = 2; k <= K; ++k) {
+                Tm[k] = fma_(di, xk, Tm[k]);
+                if (k >= 3 && k <= KN) Nm[k] = fma_(dn, xk, Nm[k]);
+                if (k < K) xk *= x;
+            }
+        }
+#pragma unroll
+        for (int k = 2; k <= K; ++k) asm volatile("" : "+v"(Tm[k]));
+#pragma unroll
+        for (int k = 3; k <= KN; ++k) asm volatile("" : "+v"(Nm[k]));
+        asm volatile("" : "+v"(xmin));
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -687,8 +807,8 @@ __device__ __attribute__((always_inline)) inline A mirror_newton(DH dH, A aL, A 
 //   G(a)  = sum_k (-1)^k T_k / (k-1) (a^(k-1) / k - 1),
 // so a Newton step costs K terms instead of a pass over the Q populations.
 // The leading term of G, T_2 (a/2 - 1), carries no cancellation, unlike the
-// difference of two sums.  With this, mirror_extended and the row-wise passes
-// of mirror_alpha the modes run at the plain step's registers and occupancy
+// difference of two sums.  With this, the extended moments and the row-wise
+// passes of mirror_alpha the modes run at the plain step's registers and occupancy
 // (F32 D3Q27: 256 -> 121 VGPRs, two -> four waves per SIMD).  150x150x120,
 // per step, in a developed near-inviscid vortex: ELBM 307 -> 204 us (F32),
 // 591 -> 338 us (FP64); one Newton step 264 -> 189 us (F32).
@@ -715,46 +835,6 @@ __device__ __attribute__((always_inline)) inline T mirror_series(const T *Tm, T 
         aL, xmin, info);
 }
 
-// alpha from the mirror condition beyond the common series' bound: one pass
-// forms the power moments to order KE in A (about 30 issue slots a
-// population; the passes of alpha_exact and mirror_alpha over rationals and
-// logarithms take about 190), for the flows whose departures are moderate.
-template <int D, typename T, typename A, bool SH, bool FULL, typename P>
-__device__ __attribute__((always_inline)) inline A mirror_extended(const P &p, const T (&d)[Lat<D>::Q], A &xmin, CellInfo &info)
-{
-    constexpr int Q = Lat<D>::Q, K = MirrorSeriesCfg<T>::KE;
-    A Tm[K + 1], N3 = A(0);
-    xmin = A(0);
-#pragma unroll
-    for (int k = 0; k <= K; ++k) Tm[k] = A(0);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        // one population at a time, as in alpha_exact
-        T g0 = gval<D, T, SH>(i, p), d0 = d[i];
-        asm volatile("" : "+v"(g0), "+v"(d0));
-        const A di = A(d0), x = di * rcp_(A(g0));
-        xmin = fmin_(xmin, x);
-        const A xn = fmin_(x, A(0));
-        N3 = fma_(di * xn, xn, N3);
-        A xk = x;
-#pragma unroll
-        for (int k = 2; k <= K; ++k) {
-            Tm[k] = fma_(di, xk, Tm[k]);
-            if (k < K) xk *= x;
-        }
-#pragma unroll
-        for (int k = 2; k <= K; ++k) asm volatile("" : "+v"(Tm[k]));
-        asm volatile("" : "+v"(N3), "+v"(xmin));
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // C1 = sum_k (-1/2)^(k-2) T_k
-    A C1 = Tm[K];
-#pragma unroll
-    for (int k = K - 1; k >= 2; --k) C1 = fma_(C1, A(-0.5), Tm[k]);
-    const A aL = conj_root(A(0.5) * N3, A(0.5) * Tm[2], C1);
-    return mirror_series<A, FULL, K>(Tm, aL, xmin, info);
-}
-
 // alpha from the mirror condition in the arithmetic type A, by passes over
 // the populations: the cells beyond the bounds of both series.
 template <int D, typename T, typename A, bool SH, bool FULL, typename P>
@@ -766,8 +846,8 @@ __device__ __attribute__((always_inline)) inline A mirror_alpha(const P &p, cons
     // many populations (a logarithm each) are live at once and spill, and one
     // at a time their dependent chains would be exposed
     auto read = [&](int i, A &g, A &di) {
-        T g0 = gval<D, T, SH>(i, p), d0 = d[i];
-        asm volatile("" : "+v"(g0), "+v"(d0));
+        T g0, d0;
+        fresh<D, T, SH>(i, p, d, g0, d0);
         g = A(g0);
         di = A(d0);
         return di * rcp_(g);
@@ -849,8 +929,6 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
     info.iters = 0;
     info.fallback = 0;
     if constexpr (MODE == MODE_BGK || MODE == MODE_LBGK) return T(2);
-    // the mirror modes start from alpha_Lower
-    constexpr int CMODE = is_mirror_mode(MODE) ? MODE_LOWER : MODE;
 
     // one pass: x, x_min, max|x| and the power moments
     // Tm[k] = <g, x^k> = sum d x^(k-1) (k = 2..K) and Nm[k] = <g, x^k>_-
@@ -884,48 +962,54 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
 #pragma unroll
     for (int k = 3; k <= K; ++k) asm volatile("" : "+v"(Nm[k]));
 
-    T alpha;
-    if (xabs < T(kGate)) {
-        alpha = T(2);  // near-equilibrium gate (App. D)
-        info.gated = 1;
-    } else if (xabs < T(SC::X)) {
-        // series of 2x^2/(2+x), x^2 N3/P3 and R(y); coefficients for x^2..x^9
-        // (the first), x^2..x^8 and y^0..y^5 (exact rationals)
-        constexpr double c1k[8] = {1.0, -0.5, 0.25, -0.125, 0.0625, -0.03125, 0.015625, -0.0078125};
-        constexpr double ck[7] = {1.0, -0.5, 1.0 / 3.0, -0.25, 0.2, -1.0 / 6.0, 57.0 / 400.0};
-        constexpr double rk[6] = {1.25, -0.625, 0.375, -0.25, 45.0 / 256.0, -65.0 / 512.0};
-        const T b1 = T(0.5) * Tm[2];
-        T C1 = T(0), C = T(0);
-#pragma unroll
-        for (int k = 2; k <= K; ++k) {
-            C1 += T(c1k[k - 2]) * Tm[k];
-            if constexpr (CMODE != MODE_LOWER) C += T(ck[k - 2]) * Tm[k];
-        }
-        const T aL = conj_root(T(0.5) * Nm[3], b1, C1);
-        if constexpr (is_mirror_mode(MODE)) {
-            alpha = mirror_series<T, MODE == MODE_ELBM, K>(Tm, aL, xmin, info);
-        } else if constexpr (CMODE == MODE_LOWER) {
-            alpha = aL;
+    T alpha = T(2);
+    if (xabs < T(SC::X)) {
+        if (xabs < T(kGate)) {
+            info.gated = 1;  // near-equilibrium gate (App. D)
         } else {
-            // Bp = sum_m r_m aL^m P_{3+m}, P_k = Tm[k] - Nm[k], by Horner
-            T Bp = T(rk[K - 3]) * (Tm[K] - Nm[K]);
-#pragma unroll
-            for (int k = K - 1; k >= 3; --k) Bp = Bp * aL + T(rk[k - 3]) * (Tm[k] - Nm[k]);
-            alpha = higher_from_coeffs(aL, b1, Bp, C, Nm[3], Nm[4], Nm[5], Nm[6], beta);
+            // series of 2x^2/(2+x), x^2 N3/P3 and R(y)
+            if constexpr (is_mirror_mode(MODE)) {
+                alpha = mirror_series<T, MODE == MODE_ELBM, K>(Tm, lower_series<T, K>(Tm, Nm), xmin, info);
+            } else if constexpr (MODE == MODE_LOWER) {
+                alpha = lower_series<T, K>(Tm, Nm);
+            } else {
+                alpha = higher_series<T, K>(Tm, Nm, beta);
+            }
         }
-    } else {
+        // positivity guard (App. D)
+        if (xmin < T(0)) {
+            const T amax = T(-1) * rcp_(beta * xmin);
+            if (alpha > amax) {
+                alpha = T(0.5) * (T(1) + amax);
+                info.guarded = 1;
+            }
+        }
+    }
+    // The cells beyond the series' bound come after the others, in a branch
+    // of their own (the empty asm keeps the compiler from joining the two):
+    // on the two sides of one branch, a wave that holds both keeps the moments
+    // above live through this one.
+    T xa = xabs;
+    asm volatile("" : "+v"(xa), "+v"(alpha));
+    if (!(xa < T(SC::X))) {
         info.exact = 1;
         // alpha and its positivity guard (App. D) in A
         A xm, al;
-        if constexpr (is_mirror_mode(MODE)) {
-            if (xabs < T(SC::XE)) {
-                al = mirror_extended<D, T, A, SH, MODE == MODE_ELBM>(p, d, xm, info);
+        constexpr bool mirror = is_mirror_mode(MODE), full = MODE == MODE_ELBM;
+        using XC = typename std::conditional<mirror, MirrorExtendedCfg<T>, ExtendedCfg<T>>::type;
+        // one of the two forms per wave: the exact one where any cell needs it
+        if (__ballot(!(xa < T(XC::X))) == 0ull) {
+            A Te[XC::K + 1], Ne[XC::K + 1];
+            extended_moments<D, T, A, SH, XC::K, MODE == MODE_HIGHER ? XC::K : 3>(p, d, Te, Ne, xm);
+            if constexpr (MODE == MODE_HIGHER) {
+                al = higher_series<A, XC::K>(Te, Ne, A(beta64));
             } else {
-                al = alpha_exact<D, T, A, CMODE, SH>(p, d, A(beta64), xm);
-                al = mirror_alpha<D, T, A, SH, MODE == MODE_ELBM>(p, d, al, xm, info);
+                al = lower_series<A, XC::K>(Te, Ne);
+                if constexpr (mirror) al = mirror_series<A, full, XC::K>(Te, al, xm, info);
             }
         } else {
-            al = alpha_exact<D, T, A, CMODE, SH>(p, d, A(beta64), xm);
+            al = alpha_exact<D, T, A, mirror ? MODE_LOWER : MODE, SH>(p, d, A(beta64), xm);
+            if constexpr (mirror) al = mirror_alpha<D, T, A, SH, full>(p, d, al, xm, info);
         }
         if (xm < A(0)) {
             const A amax = A(-1) * rcp_(A(beta64) * xm);
@@ -934,15 +1018,7 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
                 info.guarded = 1;
             }
         }
-        return T(al);
-    }
-    // positivity guard (App. D)
-    if (xmin < T(0)) {
-        const T amax = T(-1) * rcp_(beta * xmin);
-        if (alpha > amax) {
-            alpha = T(0.5) * (T(1) + amax);
-            info.guarded = 1;
-        }
+        alpha = T(al);
     }
     return alpha;
 }
