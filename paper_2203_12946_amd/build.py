@@ -4,7 +4,7 @@
 
 Every HIP source is compiled for gfx950 only, with packed-FP32 instruction
 selection disabled, to objects in parallel (the step kernel is instantiated
-once per storage type in its own source), and linked into one shared
+once per storage type and lane mapping in its own source), and linked into one shared
 library next to this file.
 """
 from __future__ import annotations
@@ -18,8 +18,9 @@ import sys
 HERE = pathlib.Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libeselbm.so"
-SOURCES = ["eselbm_step.hip", "step_f64.hip", "step_f32.hip", "step_f16s.hip", "step_f32s.hip",
-           "eselbm_adjoint.hip", "eselbm_api.hip"]
+SOURCES = ["step_f32.hip", "step_flat_f32.hip", "step_f32s.hip", "step_flat_f32s.hip", "step_f16s.hip",
+           "step_flat_f16s.hip", "step_f64.hip", "step_flat_f64.hip", "eselbm_adjoint.hip", "eselbm_step.hip",
+           "eselbm_api.hip"]
 ARCH = "gfx950"
 
 

@@ -13,8 +13,41 @@
 
 namespace eselbm {
 
+// Lanes along rows, or (flat) through whole planes.  Rows are addressed by
+// scalars; a row of partial waves, or of a short last block, wastes lanes, and
+// its stores leave partial lines.  256-lane blocks whatever the row also keep
+// the FP64 D3Q27 step at its three waves per SIMD (its 48 KiB of parked values
+// belong to a block).  Rows against planes, per step, periodic:
+//   D3Q27 F32:  250x120x130 223 / 159 us, 300x128x100 252 / 149, 320x128x100
+//               205 / 165, 100x90x110 74 / 63; 256^3 627 / 621, 128^3
+//               107.5 / 110, 64^3 13.5 / 14.1; 32^3 5.7 / 6.1;
+//   D3Q27 FP64: 48^3 27.9 / 13.0, 64^3 59 / 35, 128^3 267 / 222, 192^3 573 /
+//               568, 250x120x130 411 / 341; 16^3 6.8 / 7.2;
+//   D2Q9:       1500^2 66 / 63 (FP64), 33.5 / 30.9 (F32); 256^2 5.6 / 5.7,
+//               3.9 / 4.2; 1024^2 34.5 / 36.6, 16.7 / 16.6.
+// So planes where rows are ragged and the grid is beyond the smallest (whose
+// step is latency), and for the FP64 D3Q27 step below 256 cells a row.
+static bool use_flat(int dtype, const StepArgs &a)
+{
+    const Grid &g = a.g;
+    if ((long long)g.nx * g.ny > kMaxFlatPlane || a.walls) return false;
+    const bool ragged = g.nx % 64 != 0 || (g.nx > 256 && g.nx % 256 != 0);
+    if (g.D == 2) return ragged && g.N >= 1 << 18;
+    if (dtype == 0) return (ragged || g.nx < 256) && g.N >= 1 << 15;
+    return ragged && g.N >= 1 << 16;
+}
+
 hipError_t launch_step(int dtype, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
+    if (use_flat(dtype, a)) {
+        switch (dtype) {
+        case 0: return launch_step_flat_f64(a.g.D, mode, diag, a, s);
+        case 1: return launch_step_flat_f32(a.g.D, mode, diag, a, s);
+        case 2: return launch_step_flat_f16s(a.g.D, mode, diag, a, s);
+        case 3: return launch_step_flat_f32s(a.g.D, mode, diag, a, s);
+        }
+        return hipErrorInvalidValue;
+    }
     switch (dtype) {
     case 0: return launch_step_f64(a.g.D, mode, diag, a, s);
     case 1: return launch_step_f32(a.g.D, mode, diag, a, s);

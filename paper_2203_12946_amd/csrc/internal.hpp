@@ -38,6 +38,7 @@ struct StepArgs {
     float *uv_out;       // [D + 1][N] or null: u (with the half-force shift) and rho of the output state
     DevStats *stats;     // kStatSlots slots or null
     double cpr;          // ES-BGK stress factor c_Pr; 0: the equilibrium itself
+    double inv_nx;       // 1 / nx, for the plane-mapped launches
     int aa;              // 0: two lattices (fin -> fout); in place: 1 the pull half, 2 the local half
 };
 
@@ -48,6 +49,11 @@ hipError_t launch_step_f64(int D, int mode, bool diag, const StepArgs &a, hipStr
 hipError_t launch_step_f32(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
 hipError_t launch_step_f16s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
 hipError_t launch_step_f32s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
+// the same with the lanes running through whole planes (step_flat_<type>.hip)
+hipError_t launch_step_flat_f64(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
+hipError_t launch_step_flat_f32(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
+hipError_t launch_step_flat_f16s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
+hipError_t launch_step_flat_f32s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
 hipError_t launch_reset_stats(DevStats *st, hipStream_t s);
 hipError_t launch_init_eq(int dtype, const Grid &g, const double *rho, const double *u, void *f,
                           hipStream_t s);
@@ -99,6 +105,10 @@ hipError_t launch_dissipation_loss(LossScratch &sc, int dtype, const Grid &g, co
                                    float *force_grad, hipStream_t s);
 hipError_t launch_equilibrium_vjp(int dtype, const Grid &g, const double *rho, const double *u,
                                   const void *lam, double *grad_u, hipStream_t s);
+
+// Cells of a plane that the plane-mapped launches address by a 32-bit byte
+// offset (8-byte populations).
+constexpr long long kMaxFlatPlane = 1LL << 28;
 
 // Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx.
 inline int block_x(int nx)

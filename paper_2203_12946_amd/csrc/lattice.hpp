@@ -66,6 +66,7 @@ struct PullIndex {
         zs[2] = z == 0 ? nz_ - 1 : z - 1;
         row0 = ((long long)z * ny_ + y) * nx_;
     }
+    __host__ __device__ unsigned lane() const { return xs[1]; }  // the cell's own offset in its row
     // the row and x offset population i is pulled from: the cell - c_i
     __host__ __device__ long long src_row(int i) const
     {
@@ -79,6 +80,40 @@ struct PullIndex {
         return ((long long)zs[1 - Lat<D>::c(i, 2)] * ny + ys[1 - Lat<D>::c(i, 1)]) * nx;
     }
     __host__ __device__ unsigned dst_x(int i) const { return xs[1 - Lat<D>::c(i, 0)]; }
+};
+
+// The same for a launch whose lanes run through a whole z-plane (x, then y) and
+// not through one row: what is block-uniform is the plane, and the lane's
+// offset in it takes the place of the x offset in the row.  p is the cell's
+// offset in its plane; inv_nx is 1 / nx, with which p / nx is exact for every
+// p below 2^31 (the quotient's fraction lies 1 / (2 nx) off an integer, the
+// product's rounding below p 2^-52 / nx).
+template <int D>
+struct FlatIndex {
+    unsigned xs[3], ys[3];  // ys: element offset of the row in the plane
+    int x, y, zs[3];
+    long long plane, row0;  // row0: the cell's own plane
+    __host__ __device__ FlatIndex(unsigned p, int z, int nx, int ny, int nz, double inv_nx)
+    {
+        y = (int)(((double)p + 0.5) * inv_nx);
+        x = (int)(p - (unsigned)y * (unsigned)nx);
+        xs[0] = x + 1 == nx ? 0u : (unsigned)x + 1u;
+        xs[1] = (unsigned)x;
+        xs[2] = x == 0 ? (unsigned)nx - 1u : (unsigned)x - 1u;
+        ys[1] = (unsigned)y * (unsigned)nx;
+        ys[0] = y + 1 == ny ? 0u : ys[1] + (unsigned)nx;
+        ys[2] = y == 0 ? (unsigned)(ny - 1) * (unsigned)nx : ys[1] - (unsigned)nx;
+        plane = (long long)ny * nx;
+        zs[0] = z + 1 == nz ? 0 : z + 1;
+        zs[1] = z;
+        zs[2] = z == 0 ? nz - 1 : z - 1;
+        row0 = z * plane;
+    }
+    __host__ __device__ unsigned lane() const { return ys[1] + xs[1]; }
+    __host__ __device__ long long src_row(int i) const { return zs[Lat<D>::c(i, 2) + 1] * plane; }
+    __host__ __device__ unsigned src_x(int i) const { return ys[Lat<D>::c(i, 1) + 1] + xs[Lat<D>::c(i, 0) + 1]; }
+    __host__ __device__ long long dst_row(int i) const { return zs[1 - Lat<D>::c(i, 2)] * plane; }
+    __host__ __device__ unsigned dst_x(int i) const { return ys[1 - Lat<D>::c(i, 1)] + xs[1 - Lat<D>::c(i, 0)]; }
 };
 
 // ---------------------------------------------------------------------------

@@ -6,7 +6,7 @@ namespace eselbm {
 
 hipError_t launch_step_f16s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    return launch_step_storage<_Float16>(D, mode, diag, a, s);
+    return launch_step_storage<_Float16, false>(D, mode, diag, a, s);
 }
 
 }  // namespace eselbm

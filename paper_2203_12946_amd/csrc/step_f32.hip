@@ -6,7 +6,7 @@ namespace eselbm {
 
 hipError_t launch_step_f32(int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    return launch_step_storage<float>(D, mode, diag, a, s);
+    return launch_step_storage<float, false>(D, mode, diag, a, s);
 }
 
 }  // namespace eselbm

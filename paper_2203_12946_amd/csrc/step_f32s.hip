@@ -6,7 +6,7 @@ namespace eselbm {
 
 hipError_t launch_step_f32s(int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    return launch_step_storage<f32s>(D, mode, diag, a, s);
+    return launch_step_storage<f32s, false>(D, mode, diag, a, s);
 }
 
 }  // namespace eselbm

@@ -6,7 +6,7 @@ namespace eselbm {
 
 hipError_t launch_step_f64(int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    return launch_step_storage<double>(D, mode, diag, a, s);
+    return launch_step_storage<double, false>(D, mode, diag, a, s);
 }
 
 }  // namespace eselbm

@@ -392,7 +392,7 @@ __device__ inline void fix_x_wall(const StepArgs &a, long long cell, typename St
 // two-lattice layout.  kAAPull / kAALocal select the two launches.
 enum AAKind { kTwoLattice = 0, kAAPull = 1, kAALocal = 2 };
 
-template <int D, typename S, int MODE, bool DIAG, bool FORCE, bool WALL = false, bool QE = false, int AA = kTwoLattice>
+template <int D, typename S, int MODE, bool DIAG, bool FORCE, bool WALL = false, bool QE = false, int AA = kTwoLattice, bool FLAT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_k<D, S, MODE, WALL, QE, FORCE, AA>()))) void k_step(StepArgs a)
 {
     using T = typename Storage<S>::T;
@@ -400,8 +400,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
     constexpr int Q = Lat<D>::Q;
     const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
     const long long N = a.g.N;
-    const int y = (int)blockIdx.y, z = (int)blockIdx.z;
-    const int x = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
+    const int z = (int)blockIdx.z;
+    // the lane's offset in its row, or (FLAT) in its plane
+    const unsigned lx = blockIdx.x * blockDim.x + threadIdx.x;
     // in place the two pointers are the same buffer: no restrict there
     using InP = typename std::conditional<AA == kTwoLattice, const S *__restrict__, const S *>::type;
     using OutP = typename std::conditional<AA == kTwoLattice, S *__restrict__, S *>::type;
@@ -412,12 +413,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
     __shared__ T stash[stash_pops<D, S, MODE, WALL, QE, AA>() > 0 ? stash_pops<D, S, MODE, WALL, QE, AA>() * kStashStride : 1];
 
     LaneStats ls;
-    if (x < nx) {
+    if (lx < (unsigned)(FLAT ? nx * ny : nx)) {
         // source rows and x offsets of the pull (and, in place, the
         // neighbours the pull half stores to)
-        const PullIndex<D> pix(x, y, z, nx, ny, nz);
+        const auto pix = [&]() {
+            if constexpr (FLAT) return FlatIndex<D>(lx, z, nx, ny, nz, a.inv_nx);
+            else return PullIndex<D>((int)lx, (int)blockIdx.y, z, nx, ny, nz);
+        }();
+        const int x = [&]() { if constexpr (FLAT) return pix.x; else return (int)lx; }();
+        const int y = [&]() { if constexpr (FLAT) return pix.y; else return (int)blockIdx.y; }();
         const long long row0 = pix.row0;
-        const long long cell = row0 + x;
+        const long long cell = row0 + lx;
 
         // p: the stored values as arithmetic type -- the populations g, or
         // their deviations g - w for shifted storage.  Only p and d = feq - g
@@ -563,7 +569,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
                 Storage<S>::store_nt(lane_ptr(orow, pix.dst_x(i)), v);
             } else {
                 S *orow = fout + ((long long)i * N + row0);
-                Storage<S>::store_nt(lane_ptr(orow, (unsigned)x), v);
+                Storage<S>::store_nt(lane_ptr(orow, lx), v);
             }
         }
 
@@ -615,7 +621,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             }
         }
     }
-    if (DIAG && a.stats) block_reduce_stats(ls, a.stats + (blockIdx.y + blockIdx.z) % kStatSlots);
+    if (DIAG && a.stats) block_reduce_stats(ls, a.stats + ((FLAT ? blockIdx.x : blockIdx.y) + blockIdx.z) % kStatSlots);
 }
 
 // Occupancy cap of the D3Q27 alpha = 2 steps in the 4- and 2-byte formats.
@@ -639,13 +645,15 @@ static unsigned occupancy_cap_lds(int bx)
     return 0;
 }
 
-template <int D, typename S, int MODE>
+template <int D, typename S, int MODE, bool FLAT>
 static hipError_t launch_step_t(bool diag, const StepArgs &a, hipStream_t s)
 {
-    // (x-block, y, z); the API limits ny and nz to the grid's 65535
-    const int bx = block_x(a.g.nx);
+    // (x-block, y, z), or (plane block, 1, z); the API limits ny and nz to the
+    // grid's 65535
+    const int bx = FLAT ? 256 : block_x(a.g.nx);
     if (a.g.ny > 65535 || a.g.nz > 65535) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)((a.g.nx + bx - 1) / bx), (unsigned)a.g.ny, (unsigned)a.g.nz), block(bx);
+    const long long line = FLAT ? (long long)a.g.nx * a.g.ny : a.g.nx;
+    const dim3 grid((unsigned)((line + bx - 1) / bx), FLAT ? 1u : (unsigned)a.g.ny, (unsigned)a.g.nz), block(bx);
     const bool force = a.force != nullptr;
     if (a.aa != kTwoLattice) {
         // in place: periodic, the closed-form and alpha = 2 modes
@@ -656,13 +664,13 @@ static hipError_t launch_step_t(bool diag, const StepArgs &a, hipStream_t s)
     do {                                                                                                \
         if (force) {                                                                                    \
             if constexpr (std::is_same<S, float>::value) {                                              \
-                if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, true, false, false, KIND>), grid, block, 0, s, a);  \
-                else hipLaunchKernelGGL((k_step<D, S, MODE, false, true, false, false, KIND>), grid, block, 0, s, a);      \
+                if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, true, false, false, KIND, FLAT>), grid, block, 0, s, a);  \
+                else hipLaunchKernelGGL((k_step<D, S, MODE, false, true, false, false, KIND, FLAT>), grid, block, 0, s, a);      \
             }                                                                                           \
         } else if (diag) {                                                                              \
-            hipLaunchKernelGGL((k_step<D, S, MODE, true, false, false, false, KIND>), grid, block, 0, s, a);              \
+            hipLaunchKernelGGL((k_step<D, S, MODE, true, false, false, false, KIND, FLAT>), grid, block, 0, s, a);              \
         } else {                                                                                        \
-            hipLaunchKernelGGL((k_step<D, S, MODE, false, false, false, false, KIND>), grid, block, 0, s, a);             \
+            hipLaunchKernelGGL((k_step<D, S, MODE, false, false, false, false, KIND, FLAT>), grid, block, 0, s, a);             \
         }                                                                                               \
     } while (0)
             if (a.aa == kAAPull) ESELBM_AA_LAUNCH(kAAPull);
@@ -676,51 +684,52 @@ static hipError_t launch_step_t(bool diag, const StepArgs &a, hipStream_t s)
         // ES-BGK: periodic, unforced, path lengths alpha_Higher, alpha_Lower, 2
         if constexpr (MODE == MODE_HIGHER || MODE == MODE_LOWER || MODE == MODE_BGK) {
             if (force || a.walls) return hipErrorInvalidValue;
-            if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false, false, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_step<D, S, MODE, false, false, false, true>), grid, block, 0, s, a);
+            if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false, false, true, kTwoLattice, FLAT>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((k_step<D, S, MODE, false, false, false, true, kTwoLattice, FLAT>), grid, block, 0, s, a);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
     }
     if (a.walls) {
         if (force) return hipErrorInvalidValue;
-        if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_step<D, S, MODE, false, false, true>), grid, block, 0, s, a);
+        if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false, true, false, kTwoLattice, FLAT>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_step<D, S, MODE, false, false, true, false, kTwoLattice, FLAT>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     if (force) {
         if constexpr (std::is_same<S, float>::value) {
-            if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_step<D, S, MODE, false, true>), grid, block, 0, s, a);
+            if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, true, false, false, kTwoLattice, FLAT>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((k_step<D, S, MODE, false, true, false, false, kTwoLattice, FLAT>), grid, block, 0, s, a);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
     }
     const unsigned lds = occupancy_cap_lds<D, S, MODE>(bx);
-    if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((k_step<D, S, MODE, false, false>), grid, block, lds, s, a);
+    if (diag) hipLaunchKernelGGL((k_step<D, S, MODE, true, false, false, false, kTwoLattice, FLAT>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((k_step<D, S, MODE, false, false, false, false, kTwoLattice, FLAT>), grid, block, lds, s, a);
     return hipGetLastError();
 }
 
-template <int D, typename S>
+template <int D, typename S, bool FLAT>
 static hipError_t launch_step_m(int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
     switch (mode) {
-    case MODE_HIGHER: return launch_step_t<D, S, MODE_HIGHER>(diag, a, s);
-    case MODE_BGK: return launch_step_t<D, S, MODE_BGK>(diag, a, s);
-    case MODE_LBGK: return launch_step_t<D, S, MODE_LBGK>(diag, a, s);
-    case MODE_LOWER: return launch_step_t<D, S, MODE_LOWER>(diag, a, s);
-    case MODE_ELBM: return launch_step_t<D, S, MODE_ELBM>(diag, a, s);
-    case MODE_ITERATE1: return launch_step_t<D, S, MODE_ITERATE1>(diag, a, s);
+    case MODE_HIGHER: return launch_step_t<D, S, MODE_HIGHER, FLAT>(diag, a, s);
+    case MODE_BGK: return launch_step_t<D, S, MODE_BGK, FLAT>(diag, a, s);
+    case MODE_LBGK: return launch_step_t<D, S, MODE_LBGK, FLAT>(diag, a, s);
+    case MODE_LOWER: return launch_step_t<D, S, MODE_LOWER, FLAT>(diag, a, s);
+    case MODE_ELBM: return launch_step_t<D, S, MODE_ELBM, FLAT>(diag, a, s);
+    case MODE_ITERATE1: return launch_step_t<D, S, MODE_ITERATE1, FLAT>(diag, a, s);
     }
     return hipErrorInvalidValue;
 }
 
-// One storage type S: every lattice, mode and variant of the step.
-template <typename S>
+// One storage type S and lane mapping: every lattice, mode and variant of the
+// step.
+template <typename S, bool FLAT>
 inline hipError_t launch_step_storage(int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    return D == 2 ? launch_step_m<2, S>(mode, diag, a, s) : launch_step_m<3, S>(mode, diag, a, s);
+    return D == 2 ? launch_step_m<2, S, FLAT>(mode, diag, a, s) : launch_step_m<3, S, FLAT>(mode, diag, a, s);
 }
 
 }  // namespace eselbm

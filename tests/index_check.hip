@@ -116,6 +116,58 @@ static int run(int nx, int ny, int nz, bool full)
     return 0;
 }
 
+// The plane-mapped launch (FlatIndex): blocks of 256 lanes over the nx * ny
+// cells of each plane, every access checked as above, and every element
+// offset against the row-mapped one of the same cell.
+template <int D>
+static int run_flat(int nx, int ny, int nz, bool full)
+{
+    constexpr int Q = Lat<D>::Q;
+    const long long plane = (long long)nx * ny, N = plane * nz, QN = (long long)Q * N;
+    const long long lanes = (plane + 255) / 256 * 256;
+    const double inv_nx = 1.0 / (double)nx;
+    std::vector<unsigned char> pull, aa;
+    if (full) {
+        pull.assign((size_t)QN, 0);
+        aa.assign((size_t)QN, 0);
+    }
+    long long checked = 0;
+    const int zs[3] = {0, nz / 2, nz - 1};
+    for (int zi = 0; zi < (full ? nz : 3); ++zi) {
+        const int z = full ? zi : zs[zi];
+        // without the counts, the lanes around every row end and the last ones
+        for (long long l = 0; l < lanes; ++l) {
+            if (l >= plane) continue;  // the kernels' guard
+            if (!full && l % nx > 1 && l % nx < nx - 2 && l > 4096 && l < plane - 4096) continue;
+            const unsigned p = (unsigned)l;
+            const FlatIndex<D> f(p, z, nx, ny, nz, inv_nx);
+            const int x = (int)(l % nx), y = (int)(l / nx);
+            if (f.x != x || f.y != y || f.lane() != p) return fail("flat cell", f.lane(), plane, x, y, z, -1);
+            const PullIndex<D> r(x, y, z, nx, ny, nz);
+            for (int i = 0; i < Q; ++i) {
+                const long long lo = (long long)i * N + f.src_row(i) + f.src_x(i);
+                const long long ao = (long long)(Q - 1 - i) * N + f.dst_row(i) + f.dst_x(i);
+                if ((unsigned long long)f.src_x(i) * 8ull >= (1ull << 32)) return fail("flat lane byte offset", f.src_x(i), plane, x, y, z, i);
+                if (lo < 0 || lo >= QN || lo != (long long)i * N + r.src_row(i) + r.src_x(i)) return fail("flat pull", lo, QN, x, y, z, i);
+                if (ao < 0 || ao >= QN || ao != (long long)(Q - 1 - i) * N + r.dst_row(i) + r.dst_x(i)) return fail("flat in-place store", ao, QN, x, y, z, i);
+                if (full) {
+                    ++pull[(size_t)lo];
+                    ++aa[(size_t)ao];
+                }
+                checked += 2;
+            }
+        }
+    }
+    if (full)
+        for (long long k = 0; k < QN; ++k)
+            if (pull[(size_t)k] != 1 || aa[(size_t)k] != 1) {
+                std::printf("FAIL element %lld touched pull %d, in-place store %d times (flat)\n", k, pull[(size_t)k], aa[(size_t)k]);
+                return 1;
+            }
+    std::printf("ok %lld\n", checked);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc != 6) {
@@ -125,5 +177,7 @@ int main(int argc, char **argv)
     const int D = std::atoi(argv[1]), nx = std::atoi(argv[2]), ny = std::atoi(argv[3]), nz = std::atoi(argv[4]);
     const bool full = std::strcmp(argv[5], "full") == 0;
     if (nx < 1 || ny < 1 || nz < 1 || (D == 2 && nz != 1) || (D != 2 && D != 3)) return 2;
-    return D == 2 ? run<2>(nx, ny, nz, full) : run<3>(nx, ny, nz, full);
+    const int rc = D == 2 ? run<2>(nx, ny, nz, full) : run<3>(nx, ny, nz, full);
+    if (rc != 0 || (long long)nx * ny > kMaxFlatPlane) return rc;
+    return D == 2 ? run_flat<2>(nx, ny, nz, full) : run_flat<3>(nx, ny, nz, full);
 }

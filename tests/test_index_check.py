@@ -26,6 +26,7 @@ GRIDS = [
     (3, 128, 128, 128, "full"), (2, 256, 256, 1, "full"),     # gradient workloads
     (2, 1024, 1024, 1, "full"), (3, 256, 256, 256, "full"),   # benchmark grids
     (3, 1024, 1024, 1024, "edges"),                           # largest in-place grid
+    (3, 150, 131, 97, "full"), (2, 50000, 5003, 1, "edges"), (2, 16384, 16384, 1, "edges"),  # plane-mapped
 ]
 
 
