@@ -30,7 +30,7 @@ namespace eselbm {
 static bool use_flat(int dtype, const StepArgs &a)
 {
     const Grid &g = a.g;
-    if ((long long)g.nx * g.ny > kMaxFlatPlane || a.walls) return false;
+    if ((long long)g.nx * g.ny > kMaxFlatPlane) return false;
     const bool ragged = g.nx % 64 != 0 || (g.nx > 256 && g.nx % 256 != 0);
     if (g.D == 2) return ragged && g.N >= 1 << 18;
     if (dtype == 0) return (ragged || g.nx < 256) && g.N >= 1 << 15;

@@ -198,15 +198,16 @@ __device__ inline const auto &pick(const X &a, const Y &b)
 }
 
 // Stored values a step parks in LDS (PopAccess): the policy's count for the
-// periodic two-lattice D3Q27 steps with a closed-form path length; none for
+// two-lattice D3Q27 steps, periodic or walled (cavity 256^3 FP64: 1567 us at
+// two waves without parking, 1478 parked at three), with a path length; none for
 // alpha = 2 (BGK fits two waves' registers and is memory-bound there: parked
 // at three waves it measured 2% slower), the in-place halves (parked at
-// three waves, 3-5% slower than at two), and the walled, ES-BGK and
-// mirror-condition steps, which keep their own occupancy.
+// three waves, 3-5% slower than at two), and the ES-BGK step, which keeps its
+// own occupancy.
 template <int D, typename S, int MODE, bool WALL, bool QE, int AA>
 constexpr int stash_pops()
 {
-    return (D == 3 && !WALL && !QE && AA == 0 && (MODE == MODE_HIGHER || MODE == MODE_LOWER || is_mirror_mode(MODE))) ? StepPolicy<S>::stash : 0;
+    return (D == 3 && !QE && AA == 0 && (MODE == MODE_HIGHER || MODE == MODE_LOWER || is_mirror_mode(MODE))) ? StepPolicy<S>::stash : 0;
 }
 
 // d = feq - g of one cell, with moments and equilibrium in EQ, rounded to T,
@@ -255,9 +256,7 @@ constexpr int step_waves_qe()
 // The walled step runs the periodic pull in all but the boundary layers, so
 // it takes the periodic step's occupancy floor, at most three waves per SIMD
 // (the wall node's mass balance adds live values; the closed-form modes then
-// still fit four waves in FP32 and F16 without scratch).  The mirror-condition
-// modes, whose Newton loop already holds two waves' registers, run their
-// walled step at one.
+// still fit four waves in FP32 and F16 without scratch).
 //
 // The forced step evaluates two more equilibria (at u and u + F/rho) while d
 // and the stored values are live: at the periodic step's four waves its
@@ -279,6 +278,11 @@ constexpr int step_waves_k()
 // populations carry exactly the mass that the node's post-collision
 // populations sent into the walls.  Interior populations are pulled as in the
 // periodic case; sources outside are never loaded.
+// Straight-line code: a wall test and a load behind a branch per population
+// made the rows on a wall wait for some 60 loads in turn, about 15 us, in the
+// first plane and, worse, the last.  Per step, rows of 256-lane blocks:
+// D3Q27 cavity 256^3 752 -> 672 us (F32), 1949 -> 1571 (FP64), 531 -> 425
+// (F16-shifted); 64^3 45 -> 27 us (F32); 32^3 22 -> 12 us.
 template <int D, typename S>
 __device__ inline void pull_walls(const StepArgs &a, int x, int y, int z, typename Storage<S>::T (&p)[Lat<D>::Q])
 {
@@ -289,22 +293,24 @@ __device__ inline void pull_walls(const StepArgs &a, int x, int y, int z, typena
     const int xc[3] = {x, y, z};
     const long long N = a.g.N, cell = ((long long)z * n[1] + y) * n[0] + x;
     const S *__restrict__ fin = (const S *)a.fin;
-    // source of population i along axis k, wrapped on periodic axes;
-    // wall_of(i) = -1, or 2 k + side of the wall that emits it
-    auto src = [&](int i, int k) {
-        int v = xc[k] - Lat<D>::c(i, k);
-        if (!(a.walls >> k & 1)) v = v < 0 ? v + n[k] : (v >= n[k] ? v - n[k] : v);
-        return v;
-    };
-    auto wall_of = [&](int i) {
+    // per axis and velocity component c (at c + 1): the source coordinate,
+    // wrapped, and the wall beyond which it lies (2 k + side, -1: none);
+    // selects throughout, so that no load waits behind a branch
+    int sc[3][3], wc[3][3];
 #pragma unroll
-        for (int k = 0; k < D; ++k) {
-            if (!(a.walls >> k & 1)) continue;
-            const int v = xc[k] - Lat<D>::c(i, k);
-            if (v < 0) return 2 * k;
-            if (v >= n[k]) return 2 * k + 1;
+    for (int k = 0; k < 3; ++k) {
+        const bool walled = k < D && (a.walls >> k & 1);
+#pragma unroll
+        for (int c = -1; c <= 1; ++c) {
+            const int v = xc[k] - c, lo = v < 0, hi = v >= n[k];
+            sc[k][c + 1] = v + (lo ? n[k] : 0) - (hi ? n[k] : 0);
+            wc[k][c + 1] = c != 0 && walled && (lo || hi) ? 2 * k + hi : -1;
         }
-        return -1;
+    }
+    auto wall_of = [&](int i) {
+        const int wx = wc[0][Lat<D>::c(i, 0) + 1], wy = wc[1][Lat<D>::c(i, 1) + 1];
+        const int wz = D == 3 ? wc[2][Lat<D>::c(i, 2) + 1] : -1;
+        return wx >= 0 ? wx : (wy >= 0 ? wy : wz);
     };
     // deviations from the weights, so that the shifted formats keep their
     // precision: mass out of the node minus the weights of the outgoing
@@ -312,35 +318,40 @@ __device__ inline void pull_walls(const StepArgs &a, int x, int y, int z, typena
     // double where the storage policy forms the moments in double (the
     // re-emission is a moment computation of the wall node)
     using E = typename std::conditional<StepPolicy<S>::mom_f64, double, T>::type;
-    E out_dev = E(0), in_dev = E(0), in_w = E(0);
+    // every load before any use: the population's source, or for one that a
+    // wall re-emits, the opposite population that left this node into the
+    // same wall
+    // (masks in place of selects, which the compiler would make branches)
+    T out[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const int none = wall_of(i) >> 31;  // all ones where no wall emits it
+        const int px = x + ((sc[0][Lat<D>::c(i, 0) + 1] - x) & none);
+        const int py = y + ((sc[1][Lat<D>::c(i, 1) + 1] - y) & none);
+        const int pz = z + ((sc[2][Lat<D>::c(i, 2) + 1] - z) & none);
+        const int q = (Q - 1 - i) + ((2 * i - (Q - 1)) & none);
+        out[i] = Storage<S>::to_T(fin[q * N + ((long long)pz * n[1] + py) * n[0] + px]);
+    }
+    E out_dev = E(0), in_dev = E(0), in_w = E(0), em[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const int wl = wall_of(i);
-        if (wl < 0) {
-            const S *rowp = fin + ((long long)i * N + ((long long)src(i, 2) * n[1] + src(i, 1)) * n[0]);
-            p[i] = Storage<S>::to_T(*lane_ptr(rowp, (unsigned)src(i, 0)));
-        } else {
-            p[i] = T(0);
-            in_dev += E(a.wall_eq[wl * Q + i]);
-            in_w += E(Lat<D>::w(i));
-            // the opposite population left this node into the same wall
-            const int j = Q - 1 - i;
-            const E v = E(Storage<S>::to_T(fin[(long long)j * N + cell]));
-            out_dev += SH ? v : v - E(Lat<D>::w(j));
-        }
+        em[i] = E(a.wall_eq[(wl & ~(wl >> 31)) * Q + i]);  // feq_i(1, u_wall) - w_i
     }
-    if (in_w > E(0)) {
-        // rho_w = (in_w + out_dev) / (in_w + in_dev), as 1 + drho_w
-        const E drw = (out_dev - in_dev) * rcp_(in_w + in_dev);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const int wl = wall_of(i);
-            if (wl >= 0) {
-                const E e = E(a.wall_eq[wl * Q + i]);  // feq_i(1, u_wall) - w_i
-                const E dev = fma_(drw, E(Lat<D>::w(i)) + e, e);  // rho_w feq_i - w_i
-                p[i] = SH ? T(dev) : T(E(Lat<D>::w(i)) + dev);
-            }
-        }
+    for (int i = 0; i < Q; ++i) {
+        const bool wall = wall_of(i) >= 0;
+        in_dev += wall ? em[i] : E(0);
+        in_w += wall ? E(Lat<D>::w(i)) : E(0);
+        out_dev += wall ? (SH ? E(out[i]) : E(out[i]) - E(Lat<D>::w(Q - 1 - i))) : E(0);
+    }
+    // rho_w = (in_w + out_dev) / (in_w + in_dev), as 1 + drho_w
+    const E drw = (out_dev - in_dev) * rcp_(in_w + in_dev);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const E dev = fma_(drw, E(Lat<D>::w(i)) + em[i], em[i]);  // rho_w feq_i - w_i
+        const T emitted = SH ? T(dev) : T(E(Lat<D>::w(i)) + dev);
+        p[i] = wall_of(i) >= 0 ? emitted : out[i];
     }
 }
 
