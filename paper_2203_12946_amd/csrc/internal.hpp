@@ -39,6 +39,7 @@ struct StepArgs {
     DevStats *stats;     // kStatSlots slots or null
     double cpr;          // ES-BGK stress factor c_Pr; 0: the equilibrium itself
     double inv_nx;       // 1 / nx, for the plane-mapped launches
+    int cached;          // plain stores, else non-temporal ones (cached_stores)
     int aa;              // 0: two lattices (fin -> fout); in place: 1 the pull half, 2 the local half
 };
 
@@ -109,6 +110,28 @@ hipError_t launch_equilibrium_vjp(int dtype, const Grid &g, const double *rho, c
 // Cells of a plane that the plane-mapped launches address by a 32-bit byte
 // offset (8-byte populations).
 constexpr long long kMaxFlatPlane = 1LL << 28;
+
+// Plain stores of a step's output (true), or non-temporal ones, which stream
+// past the caches.  Streaming is the faster way out of a grid whose two
+// lattices exceed the 256 MB last-level cache, and out of a small one, whose
+// dirty lines the L2s would write back at the end of the launch.  Plain stores
+// are faster
+//  - where the two lattices fit the last-level cache, from which the next step
+//    then reads (per step, streaming / plain: D2Q9 1024^2 FP64 34.7 / 26.1 us,
+//    F32 16.6 / 15.1, 1000^2 F32 15.7 / 14.0, 2048^2 F16-shifted 34.0 / 30.6;
+//    D3Q27 128^3 F16-shifted 53.1 / 47.1; at their other side 512^2 F32 6.0 /
+//    7.4, 64^3 F32 19.8 / 21.5, 1500^2 FP64 60 / 64, 256^3 F32 629 / 657);
+//  - where the populations' fields do not start on cache lines (N elements no
+//    multiple of 128 bytes): a wave's row then ends in the middle of a line,
+//    which streams out in two partial writes and merges in the L2 (255x253x251
+//    F32 979 / 805 us, FP64 1732 / 1558, F16-shifted 558 / 439; 203x97x131 F32
+//    141 / 130; 101x99x97 F32 54 / 46).
+inline bool cached_stores(const Grid &g, int elem)
+{
+    const long long bytes = 2LL * g.Q * g.N * elem;
+    if (bytes < (g.D == 2 ? 55000000LL : 110000000LL)) return false;
+    return g.N * elem % 128 != 0 || bytes <= (256LL << 20);
+}
 
 // Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx.
 inline int block_x(int nx)

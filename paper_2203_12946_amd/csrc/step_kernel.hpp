@@ -570,18 +570,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             }
         }
         // post-collision value p + alpha beta (feq - g) [+ force term]
+        auto put = [&](auto store) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const T v = Pol::ab_split || FORCE ? fma_(ab, dd[i], fma_(ab_lo, dd[i], pa[i])) : fma_(ab, dd[i], pa[i]);
-            if constexpr (AA == kAAPull) {
-                // slot opp(i) of cell x + c_i, the location this lane read
-                // population opp(i) from
-                S *orow = fout + ((long long)(Q - 1 - i) * N + pix.dst_row(i));
-                Storage<S>::store_nt(lane_ptr(orow, pix.dst_x(i)), v);
-            } else {
-                S *orow = fout + ((long long)i * N + row0);
-                Storage<S>::store_nt(lane_ptr(orow, lx), v);
+            for (int i = 0; i < Q; ++i) {
+                const T v = Pol::ab_split || FORCE ? fma_(ab, dd[i], fma_(ab_lo, dd[i], pa[i])) : fma_(ab, dd[i], pa[i]);
+                if constexpr (AA == kAAPull) {
+                    // slot opp(i) of cell x + c_i, the location this lane read
+                    // population opp(i) from
+                    store(lane_ptr(fout + ((long long)(Q - 1 - i) * N + pix.dst_row(i)), pix.dst_x(i)), v);
+                } else {
+                    store(lane_ptr(fout + ((long long)i * N + row0), lx), v);
+                }
             }
+        };
+        // (the empty asm around one of them keep the compiler from joining the
+        // branches' stores, by hoisting or sinking, and dropping the hint)
+        if (a.cached) {
+            asm volatile("; cached stores");
+            put([](S *q, T v) { Storage<S>::store(q, v); });
+            asm volatile("; end of cached stores");
+        } else {
+            put([](S *q, T v) { Storage<S>::store_nt(q, v); });
         }
 
         // the velocity and density of the output state, for a loss that
