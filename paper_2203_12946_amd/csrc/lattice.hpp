@@ -189,6 +189,18 @@ __device__ inline S *lane_ptr(S *row, unsigned xi)
     return (S *)((char *)row + xi * (unsigned)sizeof(S));
 }
 
+// A block-uniform 64-bit offset as a scalar (readfirstlane of each half, which
+// costs nothing on a value already in scalar registers): the compiler then
+// cannot fold the lane's offset into it, which would make every access of a
+// row a 64-bit per-lane sum.
+__device__ inline long long uniform64(long long o)
+{
+    const unsigned long long u = (unsigned long long)o;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
 // Fast reciprocal / square root: v_rcp_f32 and v_sqrt_f32 (about 1 ulp) in
 // single precision, correctly rounded operations in double precision.
 __device__ inline float rcp_(float v) { return __builtin_amdgcn_rcpf(v); }

@@ -486,10 +486,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
         E drhoE, jE[3];
         row_moments<D, E>([&](int i) { return E(dev(i)); }, drhoE, jE);
         // positivity by comparisons (a min over raw loaded values would make
-        // the compiler keep quieted copies of all of them)
+        // the compiler keep quieted copies of all of them); of a shifted value
+        // against -w, which has the sign of w + p without the sum
         bool pos = true;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) pos = pos && (gval<D, T, SH>(i, p) > T(0));
+        for (int i = 0; i < Q; ++i) pos = pos && (p[i] > (SH ? -T(Lat<D>::w(i)) : T(0)));
         // from here on the stored values are read through pa: in registers,
         // or mostly parked in LDS (the empty asm's memory clobber keeps the
         // compiler from forwarding the parked registers to their reads)
@@ -571,22 +572,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
         }
         // post-collision value p + alpha beta (feq - g) [+ force term]
         auto put = [&](auto store) {
+            // (the fields' distance as a value of this branch's own: shared,
+            // the Q field addresses are formed ahead of the branch and spill)
+            long long n1 = N;
+            asm volatile("" : "+s"(n1));
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 const T v = Pol::ab_split || FORCE ? fma_(ab, dd[i], fma_(ab_lo, dd[i], pa[i])) : fma_(ab, dd[i], pa[i]);
                 if constexpr (AA == kAAPull) {
                     // slot opp(i) of cell x + c_i, the location this lane read
                     // population opp(i) from
-                    store(lane_ptr(fout + ((long long)(Q - 1 - i) * N + pix.dst_row(i)), pix.dst_x(i)), v);
+                    store(lane_ptr(fout + uniform64((Q - 1 - i) * n1 + pix.dst_row(i)), pix.dst_x(i)), v);
                 } else {
-                    store(lane_ptr(fout + ((long long)i * N + row0), lx), v);
+                    store(lane_ptr(fout + uniform64(i * n1 + row0), lx), v);
                 }
             }
         };
-        // (the empty asm around one of them keep the compiler from joining the
-        // branches' stores, by hoisting or sinking, and dropping the hint)
+        // (the empty asm keeps the compiler from joining the branches' stores
+        // and dropping the hint)
         if (a.cached) {
-            asm volatile("; cached stores");
             put([](S *q, T v) { Storage<S>::store(q, v); });
             asm volatile("; end of cached stores");
         } else {
