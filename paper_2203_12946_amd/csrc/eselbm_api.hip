@@ -267,16 +267,23 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
     }
     hipStream_t s = (hipStream_t)stream;
     // Step k reads one buffer and writes the other, starting f_in -> f_out;
-    // after an even count the newest state is back in f_in and one copy
-    // moves it to f_out (f_in is documented as clobbered).  In place
+    // after an even count the newest state is back in f_in.  In place
     // (f_in == f_out) the steps alternate the pull half and the local half
-    // of the AA pattern on the one buffer.
+    // of the AA pattern on the one buffer.  An even count on two lattices
+    // ends with such a pair in f_in, whose local half writes f_out as well;
+    // the walled, ES-BGK and mirror-condition steps, which have no in-place
+    // form, copy the state to f_out instead.
+    const bool pair = !in_place && nsteps % 2 == 0 && !h->walls && cpr == 0.0 &&
+                      h->mode != ESELBM_MODE_ELBM && h->mode != ESELBM_MODE_ITERATE1;
     void *src = f_in, *dst = f_out;
     for (int k = 0; k < nsteps; ++k) {
         const bool last = k == nsteps - 1;
+        const bool aa = in_place || (pair && k >= nsteps - 2);
+        if (aa) dst = src;
         StepArgs sa;
         sa.fin = src;
         sa.fout = dst;
+        sa.fout2 = pair && last ? f_out : nullptr;
         sa.g = h->g;
         sa.beta = 1.0 / (2.0 * tau + 1.0);
         sa.force = h->force;
@@ -289,7 +296,7 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         sa.cpr = cpr;
         sa.inv_nx = 1.0 / (double)h->g.nx;
         sa.cached = !in_place && cached_stores(h->g, (int)elem_size(h->dtype));
-        sa.aa = in_place ? (k % 2 == 0 ? 1 : 2) : 0;
+        sa.aa = aa ? (k % 2 == 0 ? 1 : 2) : 0;
         // the forced step writes the velocity field itself; the others do it
         // in their diagnostic variant
         const bool diag = sa.alpha_out != nullptr || sa.nut_out != nullptr || sa.stats != nullptr ||
@@ -300,13 +307,13 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         }
         hipError_t e = launch_step(h->dtype, h->mode, diag, sa, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_step: launch");
-        if (!in_place) {
+        if (!aa) {
             void *t = src;
             src = dst;
             dst = t;
         }
     }
-    if (src != f_out) {
+    if (src != f_out && !pair) {
         hipError_t e = hipMemcpyAsync(f_out, src, bytes, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_step: copy");
     }

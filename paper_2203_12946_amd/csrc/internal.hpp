@@ -28,6 +28,7 @@ struct Grid {
 struct StepArgs {
     const void *fin;
     void *fout;
+    void *fout2;  // or null; in place, the local half's output once more
     Grid g;
     double beta;
     const float *force;  // [D][N] or null

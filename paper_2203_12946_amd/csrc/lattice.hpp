@@ -125,8 +125,8 @@ struct Storage;
 
 // kShifted: the stored value is the deviation g - w itself, else the
 // population g.  to_T converts a stored value to the arithmetic type;
-// full() gives the population in double for diagnostics; store writes, and
-// store_nt writes with the non-temporal hint (cached_stores chooses).
+// full() gives the population in double for diagnostics; store_nt writes
+// with the non-temporal hint (cached_stores chooses).
 template <>
 struct Storage<double> {
     using T = double;
@@ -134,8 +134,7 @@ struct Storage<double> {
     __device__ static T to_T(double s) { return s; }
     __device__ static double from_T(T v) { return v; }
     __device__ static double full(double s, double) { return s; }
-    __device__ static void store(double *p, T v) { *p = v; }
-    __device__ static void store_nt(double *p, T v) { __builtin_nontemporal_store(v, p); }
+    __device__ static void store_nt(double *p, double v) { __builtin_nontemporal_store(v, p); }
 };
 
 template <>
@@ -145,8 +144,7 @@ struct Storage<float> {
     __device__ static T to_T(float s) { return s; }
     __device__ static float from_T(T v) { return v; }
     __device__ static double full(float s, double) { return (double)s; }
-    __device__ static void store(float *p, T v) { *p = v; }
-    __device__ static void store_nt(float *p, T v) { __builtin_nontemporal_store(v, p); }
+    __device__ static void store_nt(float *p, float v) { __builtin_nontemporal_store(v, p); }
 };
 
 // single-precision deviations f - w (the F32-shifted storage type)
@@ -161,8 +159,7 @@ struct Storage<f32s> {
     __device__ static T to_T(f32s s) { return s.v; }
     __device__ static f32s from_T(T v) { return f32s{v}; }
     __device__ static double full(f32s s, double w) { return w + (double)s.v; }
-    __device__ static void store(f32s *p, T v) { p->v = v; }
-    __device__ static void store_nt(f32s *p, T v) { __builtin_nontemporal_store(v, &p->v); }
+    __device__ static void store_nt(f32s *p, f32s v) { __builtin_nontemporal_store(v.v, &p->v); }
 };
 
 template <>
@@ -172,8 +169,7 @@ struct Storage<_Float16> {
     __device__ static T to_T(_Float16 s) { return (float)s; }
     __device__ static _Float16 from_T(T v) { return (_Float16)v; }
     __device__ static double full(_Float16 s, double w) { return w + (double)(float)s; }
-    __device__ static void store(_Float16 *p, T v) { *p = (_Float16)v; }
-    __device__ static void store_nt(_Float16 *p, T v) { __builtin_nontemporal_store((_Float16)v, p); }
+    __device__ static void store_nt(_Float16 *p, _Float16 v) { __builtin_nontemporal_store(v, p); }
 };
 
 // Block-uniform row pointer plus a 32-bit per-lane byte offset: the form

@@ -108,3 +108,32 @@ def test_in_place_rejections(es):
     s.set_walls([True, True])
     with pytest.raises(es.EselbmError):
         s.step(a, a, 2, 0.1)
+
+
+@pytest.mark.parametrize("n", [2, 4])
+@pytest.mark.parametrize("D,shape", [(2, (9, 70)), (2, (530, 517)), (3, (6, 9, 70)), (3, (41, 43, 44))])
+@pytest.mark.parametrize("dtype,mode", [("f64", "higher"), ("f32", "higher"), ("f32s", "lower"), ("f16s", "higher"),
+                                        ("f32", "bgk"), ("f32", "lbgk"), ("f32", "elbm")])
+def test_even_counts_leave_the_state_in_both(es, D, shape, dtype, mode, n):
+    """An even count equals the same steps one by one, to the bit, in f_out and
+    in f_in, with its statistics and fields those of the last step."""
+    s = es.Solver("D2Q9" if D == 2 else "D3Q27", shape, dtype=dtype, mode=mode)
+    if dtype == "f32" and mode == "higher":
+        s.set_force(torch.from_numpy(W.random_force(shape, D, amplitude=1e-4)).float().cuda())
+    a = _upload(s, three_regime_state(D, shape, 4), dtype)
+    one, nxt = a.clone(), s.empty_state()
+    uv1 = s.empty_velocity()
+    for k in range(n):
+        s.set_stats(k == n - 1)
+        s.set_velocity_field(uv1 if k == n - 1 else None)
+        s.step(one, nxt, 1, 3e-3)
+        one, nxt = nxt, one
+    ref = s.stats()
+    b, uv = s.empty_state(), s.empty_velocity()
+    s.set_velocity_field(uv)
+    s.step(a, b, n, 3e-3)
+    st = s.stats()
+    assert torch.equal(one, b) and torch.equal(one, a)
+    for k in ("n_cells", "n_gated", "n_exact", "n_guard", "n_nonpos"):
+        assert st[k] == ref[k]
+    assert torch.equal(torch.nan_to_num(uv, nan=9.0), torch.nan_to_num(uv1, nan=9.0))
