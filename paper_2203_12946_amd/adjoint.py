@@ -66,14 +66,29 @@ class Rollout:
         self.tail: dict[int, tuple[torch.Tensor, torch.Tensor | None]] = {}
         self.uv_end: torch.Tensor | None = None
 
-    def _step_with_velocity(self, f: torch.Tensor, out: torch.Tensor, uv: torch.Tensor):
-        """One step f -> out that also writes out's velocity field into uv."""
+    def _steps(self, f: torch.Tensor, outs: list, uvs: list | None = None, loss: torch.Tensor | None = None):
+        """One step f -> outs[0] -> outs[1] ... each; with ``uvs`` the velocity
+        field of each, with ``loss`` (and ``uvs``) its dissipation loss added.
+        One native call where the solver has it: on a small lattice the
+        Python call of a step takes longer than the step."""
         s = self.s
-        s.set_velocity_field(uv)
-        try:
-            s.step(f, out, 1, self.tau)
-        finally:
-            s.set_velocity_field(None)
+        if not outs:
+            return
+        if hasattr(s, "step_series"):
+            s.step_series(f, outs, self.tau, uvs, loss if uvs is not None else None, self.diss_weight or 0.0)
+            return
+        for k, out in enumerate(outs):
+            if uvs is None:
+                s.step(f, out, 1, self.tau)
+            else:
+                s.set_velocity_field(uvs[k])
+                try:
+                    s.step(f, out, 1, self.tau)
+                finally:
+                    s.set_velocity_field(None)
+                if loss is not None:
+                    s.dissipation_loss_uv(uvs[k], loss=loss, weight=self.diss_weight)
+            f = out
 
     def _last_start(self) -> int:
         """First state of the last checkpoint segment."""
@@ -118,34 +133,35 @@ class Rollout:
         with_loss = self.diss_weight is not None and loss_acc is not None
         uv = s.empty_velocity() if with_loss else None
         first = self._kept_start()
-        for n in range(self.nsteps):
-            m = n + 1  # the state this step produces
+        # steps are handed over a checkpoint segment at a time (up to ``stop``)
+        start = 0
+        while start < self.nsteps:
+            stop = min(start + self.K, self.nsteps)
             # the states after the first kept segment's checkpoint, and the
             # final one, get buffers of their own (the former are kept for
             # the backward)
-            fresh = m > first
-            keep = first < m < self.nsteps
-            out = s.empty_state() if fresh else nxt
-            out_uv = None
-            if with_loss:
-                out_uv = s.empty_velocity() if (keep or m == first) else uv
-                self._step_with_velocity(cur, out, out_uv)
-                s.dissipation_loss_uv(out_uv, loss=loss_acc, weight=self.diss_weight)
-            else:
-                s.step(cur, out, 1, self.tau)
-            if fresh:
-                cur = out
-            else:
-                cur, nxt = out, cur
-            if keep and m % self.K != 0:
-                self.tail[m] = (out, out_uv)
-            if m % self.K == 0 and m < self.nsteps:
+            outs, uvs, src = [], [], cur
+            for m in range(start + 1, stop + 1):
+                keep = first < m < self.nsteps
+                fresh = m > first
+                out = s.empty_state() if fresh else nxt
+                if not fresh:
+                    nxt = src
+                outs.append(out)
+                uvs.append((s.empty_velocity() if (keep or m == first) else uv) if with_loss else None)
+                if keep and m % self.K != 0:
+                    self.tail[m] = (out, uvs[-1])
+                src = out
+            self._steps(cur, outs, uvs if with_loss else None, loss_acc)
+            cur = src
+            if stop % self.K == 0 and stop < self.nsteps:
                 # a kept state's buffer is never written again
-                self.ckpts[m] = cur if fresh else cur.clone()
+                self.ckpts[stop] = cur if stop > first else cur.clone()
                 if with_loss:
-                    self.ckpt_uv[m] = out_uv if (keep or m == first) else out_uv.clone()
+                    self.ckpt_uv[stop] = uvs[-1] if stop >= first else uvs[-1].clone()
+            start = stop
         if with_loss:
-            self.uv_end = out_uv
+            self.uv_end = uvs[-1]
         return cur
 
     def backward(self, lam_final: torch.Tensor | None, diss_grad: float = 0.0,
@@ -193,35 +209,40 @@ class Rollout:
             states = [self.ckpts[start]]
             uvs = [self.ckpt_uv.get(start)]
             kept = all(m in self.tail for m in range(start + 1, stop))
-            for m in range(start + 1, stop):
-                if kept:
-                    states.append(self.tail[m][0])
-                    uvs.append(self.tail[m][1])
-                    continue
-                nxt = s.empty_state()
-                if w:
-                    uvs.append(s.empty_velocity())
-                    self._step_with_velocity(states[-1], nxt, uvs[-1])
-                else:
-                    uvs.append(None)
-                    s.step(states[-1], nxt, 1, self.tau)
-                states.append(nxt)
+            if kept:
+                states += [self.tail[m][0] for m in range(start + 1, stop)]
+                uvs += [self.tail[m][1] for m in range(start + 1, stop)]
+            else:
+                fresh = [s.empty_state() for _ in range(start + 1, stop)]
+                fuv = [s.empty_velocity() for _ in fresh] if w else None
+                self._steps(states[0], fresh, fuv)
+                states += fresh
+                uvs += fuv if w else [None] * len(fresh)
             if kept:
                 # the kept states now live in this segment's list only, so
                 # they are freed with it, segment by segment (a later
                 # backward of the same forward recomputes them)
                 for m in range(start + 1, stop):
                     del self.tail[m]
-            for n in range(stop - 1, start - 1, -1):
-                f_n = states[n - start]
-                if pend_uv is not None:
-                    s.adjoint_step_diss(f_n, lam, pend_uv, w, other, self.tau, force_grad=force_grad)
-                else:
-                    s.adjoint_step(f_n, lam, other, self.tau, force_grad=force_grad, seed_next=pend_seed)
-                lam, other = other, lam
-                pend_seed = pend_uv = None
-                if w and n >= 1:
-                    seed_of(f_n, uvs[n - start])
+            # the seed of the state after each step: none, or formed in the
+            # step from its velocity field, or (w without such a field, or in
+            # double precision) by a pass of its own
+            if hasattr(s, "adjoint_series") and pend_seed is None and (
+                    not w or (fused and all(u is not None for u in uvs[1:]) and (start == 0 or uvs[0] is not None))):
+                lam, other = s.adjoint_series(states[::-1], lam, other, self.tau,
+                                              [pend_uv] + uvs[:0:-1] if w else None, w or 0.0, force_grad)
+                pend_uv = uvs[0] if w and start >= 1 else None
+            else:
+                for n in range(stop - 1, start - 1, -1):
+                    f_n = states[n - start]
+                    if pend_uv is not None:
+                        s.adjoint_step_diss(f_n, lam, pend_uv, w, other, self.tau, force_grad=force_grad)
+                    else:
+                        s.adjoint_step(f_n, lam, other, self.tau, force_grad=force_grad, seed_next=pend_seed)
+                    lam, other = other, lam
+                    pend_seed = pend_uv = None
+                    if w and n >= 1:
+                        seed_of(f_n, uvs[n - start])
             del states, uvs
             n_end = start
         return lam

@@ -3,6 +3,7 @@
 // happens here; every computation is a kernel enqueued on the caller's
 // stream.
 #include "../../include/eselbm.h"
+#include "../../include/eselbm_rollout.h"
 #include "internal.hpp"
 
 #include <cmath>
@@ -511,6 +512,43 @@ eselbm_status eselbm_equilibrium_vjp(eselbm_handle h, const double *rho, const d
     hipError_t e = launch_equilibrium_vjp(h->dtype, h->g, rho, u, lam, grad_u, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "eselbm_equilibrium_vjp: launch");
     return ESELBM_OK;
+}
+
+eselbm_status eselbm_rollout_steps(eselbm_handle h, const void *f, void *const *states, float *const *uvs, int n,
+                                   double tau, double *loss_dev, double weight, void *stream)
+{
+    if (!h || !f || !states) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: NULL argument");
+    if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: n must be >= 1");
+    if (loss_dev && !uvs) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: the loss needs velocity fields");
+    eselbm_status st = ESELBM_OK;
+    void *src = const_cast<void *>(f);  // one step at a time: eselbm_step does not write its input
+    for (int k = 0; k < n && st == ESELBM_OK; ++k) {
+        if (uvs) h->uv_field = uvs[k];
+        st = states[k] == src ? fail(ESELBM_E_ARG, "eselbm_rollout_steps: a step onto its own input")
+                              : eselbm_step(h, src, states[k], 1, tau, stream);
+        if (st == ESELBM_OK && loss_dev)
+            st = eselbm_dissipation_loss_uv(h, uvs[k], loss_dev, nullptr, nullptr, weight, nullptr, stream);
+        src = states[k];
+    }
+    if (uvs) h->uv_field = nullptr;
+    return st;
+}
+
+eselbm_status eselbm_rollout_adjoints(eselbm_handle h, const void *const *states, const float *const *uvs, int n,
+                                      double weight, void *lam, void *other, double tau, void *force_grad,
+                                      void *stream)
+{
+    if (!h || !states || !lam || !other) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: NULL argument");
+    if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: n must be >= 1");
+    eselbm_status st = ESELBM_OK;
+    for (int k = 0; k < n && st == ESELBM_OK; ++k) {
+        st = uvs && uvs[k] ? eselbm_adjoint_step_diss(h, states[k], lam, uvs[k], weight, other, tau, force_grad, stream)
+                           : eselbm_adjoint_step(h, states[k], lam, nullptr, other, tau, force_grad, stream);
+        void *t = lam;
+        lam = other;
+        other = t;
+    }
+    return st;
 }
 
 }  // extern "C"

@@ -78,6 +78,11 @@ _SIGNATURES = {
     "eselbm_equilibrium_vjp": [_vp, _vp, _vp, _vp, _vp, _vp],
 }
 EXPORTS = tuple(_SIGNATURES) + ("eselbm_last_error",)
+# include/eselbm_rollout.h: a rollout's sequences of the calls above
+_ROLLOUT_SIGNATURES = {
+    "eselbm_rollout_steps": [_vp, _vp, _vp, _vp, ctypes.c_int, ctypes.c_double, _vp, ctypes.c_double, _vp],
+    "eselbm_rollout_adjoints": [_vp, _vp, _vp, ctypes.c_int, ctypes.c_double, _vp, _vp, ctypes.c_double, _vp, _vp],
+}
 
 
 def _load() -> ctypes.CDLL:
@@ -86,7 +91,7 @@ def _load() -> ctypes.CDLL:
             f"{_LIB_PATH} is not built; run `python -m paper_2203_12946_amd.build` "
             "(there is no CPU fallback)")
     lib = ctypes.CDLL(str(_LIB_PATH))
-    for name, argtypes in _SIGNATURES.items():
+    for name, argtypes in {**_SIGNATURES, **_ROLLOUT_SIGNATURES}.items():
         fn = getattr(lib, name)
         fn.argtypes = argtypes
         fn.restype = ctypes.c_int
@@ -303,6 +308,44 @@ class Solver:
                 self._p(lam_n, self.compute_dtype, n), float(tau),
                 self._p(force_grad, torch.float32, self.D * self.cells) if force_grad is not None else _vp(None),
                 _stream(stream)))
+
+    # ---- a rollout's sequences (include/eselbm_rollout.h) -----------------
+    @staticmethod
+    def _pointers(tensors):
+        return (_vp * len(tensors))(*[None if t is None else t.data_ptr() for t in tensors])
+
+    def step_series(self, f, outs, tau: float, uvs=None, loss=None, weight: float = 0.0, stream=None):
+        """One step f -> outs[0] -> outs[1] ... each; with ``uvs`` the velocity
+        field of each, with ``loss`` its dissipation loss added."""
+        n = self.Q * self.cells
+        for t in outs:
+            self._p(t, self.storage_dtype, n)
+        for t in uvs or ():
+            self._p(t, torch.float32, (self.D + 1) * self.cells)
+        if uvs is not None:
+            self._uv = None
+        with self._on():
+            _check(lib.eselbm_rollout_steps(
+                self._h, self._p(f, self.storage_dtype, n), self._pointers(outs),
+                None if uvs is None else self._pointers(uvs), len(outs), float(tau), self._p(loss, torch.float64, 1),
+                float(weight), _stream(stream)))
+
+    def adjoint_series(self, states, lam, other, tau: float, uvs=None, weight: float = 0.0, force_grad=None,
+                       stream=None):
+        """The adjoint steps of ``states`` (newest first) from ``lam``, with
+        the dissipation seed of ``uvs[k]`` where that is not None; returns
+        (the buffer that holds the result, the other one)."""
+        n = self.Q * self.cells
+        for t in states:
+            self._p(t, self.storage_dtype, n)
+        for t in uvs or ():
+            self._p(t, torch.float32, (self.D + 1) * self.cells)
+        with self._on():
+            _check(lib.eselbm_rollout_adjoints(
+                self._h, self._pointers(states), None if uvs is None else self._pointers(uvs), len(states),
+                float(weight), self._p(lam, self.compute_dtype, n), self._p(other, self.compute_dtype, n), float(tau),
+                self._p(force_grad, torch.float32, self.D * self.cells), _stream(stream)))
+        return (lam, other) if len(states) % 2 == 0 else (other, lam)
 
     def kinetic_loss(self, f, loss=None, lam=None, scale: float = 1.0, stream=None):
         with self._on():
