@@ -257,16 +257,12 @@ constexpr int step_waves_qe()
 // it takes the periodic step's occupancy floor, at most three waves per SIMD
 // (the wall node's mass balance adds live values; the closed-form modes then
 // still fit four waves in FP32 and F16 without scratch).
-//
-// The forced step evaluates two more equilibria (at u and u + F/rho) while d
-// and the stored values are live: at the periodic step's four waves its
-// common path would spill, so it runs at three.
-template <int D, typename S, int MODE, bool WALL, bool QE, bool FORCE, int AA>
+template <int D, typename S, int MODE, bool WALL, bool QE, int AA>
 constexpr int step_waves_k()
 {
     return stash_pops<D, S, MODE, WALL, QE, AA>() > 0 ? StepPolicy<S>::stash_waves
            : WALL ? (step_waves_qe<D, S, MODE, QE>() > 3 ? 3 : step_waves_qe<D, S, MODE, QE>())
-                  : (FORCE && step_waves_qe<D, S, MODE, QE>() > 3 ? 3 : step_waves_qe<D, S, MODE, QE>());
+                  : step_waves_qe<D, S, MODE, QE>();
 }
 
 // Pull with diffuse walls (the boundary rule of the lid-driven cavity,
@@ -408,7 +404,7 @@ __device__ inline void fix_x_wall(const StepArgs &a, long long cell, typename St
 enum AAKind { kTwoLattice = 0, kAAPull = 1, kAALocal = 2 };
 
 template <int D, typename S, int MODE, bool DIAG, bool FORCE, bool WALL = false, bool QE = false, int AA = kTwoLattice, bool FLAT = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_k<D, S, MODE, WALL, QE, FORCE, AA>()))) void k_step(StepArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_k<D, S, MODE, WALL, QE, AA>()))) void k_step(StepArgs a)
 {
     using T = typename Storage<S>::T;
     using Pol = StepPolicy<S>;
@@ -555,12 +551,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             if (FORCE) {
                 const T ir = rcp_(rho);
                 const T u[3] = {quot_(j[0], rho, ir), quot_(j[1], rho, ir), D == 3 ? quot_(j[2], rho, ir) : T(0)};
-                T uf[3] = {u[0], u[1], u[2]};
+                T du[3] = {T(0), T(0), T(0)};
 #pragma unroll
-                for (int c = 0; c < D; ++c) uf[c] += (T)a.force[(long long)c * N + cell] * ir;
-                const Equilibrium<D, T> eq(drho, u), eqf(drho, uf);
+                for (int c = 0; c < D; ++c) du[c] = (T)a.force[(long long)c * N + cell] * ir;
 #pragma unroll
-                for (int i = 0; i < Q; ++i) dd[i] = (ab + ab_lo) * dd[i] + (eqf.dev(i) - eq.dev(i));
+                for (int i = 0; i < Q; ++i) dd[i] = (ab + ab_lo) * dd[i];
+                ForceTerm<D, T>(rho, u, du).add(dd);
                 ab = T(1);
                 ab_lo = T(0);
             }
