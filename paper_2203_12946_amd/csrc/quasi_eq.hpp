@@ -193,45 +193,188 @@ struct QECfg<double> {
     static constexpr int maxit = 50;
 };
 
-// Replaces d = feq - g by f^QE - g.  p holds the stored values (g, or g - w
-// when SH), d the deviation of the equilibrium; E is the arithmetic type of
-// the solve.  Returns false when Newton does not converge (the target
-// pressure lies beyond what positive populations carry): d is then left
-// as the equilibrium's.  iters receives the Newton iterations.
-template <int D, typename T, typename E, bool SH>
-__device__ inline bool quasi_equilibrium(const T (&p)[Lat<D>::Q], T (&d)[Lat<D>::Q], E cpr, int &iters)
+// true in every lane when every lane's exponents delta . phi_i are within the
+// range of expm1_small (a wave-uniform choice, so that the wave takes one of
+// the two forms)
+template <int K, typename E>
+__device__ inline bool small_exponents(const E (&dl)[K])
+{
+    E bound = E(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) bound += abs_(dl[k]);
+    return __ballot(!(bound <= E(kSmallExpArg))) == 0ull;
+}
+
+// out(i, r_i) of r_i = feq_i expm1(delta . phi_i)
+template <int D, typename E, typename FE, typename OUT>
+__device__ inline void qe_excess(const E (&delta)[QEBasis<D>::K], FE fe, OUT out)
+{
+    const QEArgs<D, E> qa(delta);
+    if (small_exponents(delta)) {
+#pragma unroll
+        for (int i = 0; i < Lat<D>::Q; ++i) out(i, fe(i) * expm1_small(qa(i)));
+    } else {
+#pragma unroll
+        for (int i = 0; i < Lat<D>::Q; ++i) out(i, fe(i) * expm1_(qa(i)));
+    }
+}
+
+// The inverse of the Jacobian at delta = 0, J0 = sum_i feq_i phi_i phi_i^T, in
+// closed form.  The equilibrium is a product over the axes, so under it the
+// c_a are independent, and in the basis
+//   1, v_a = c_a - u_a, v_a v_b, q_a = c_a^2 - s_a - k_a v_a,
+//   s_a = <c_a^2>, V_a = s_a - u_a^2, k_a = u_a (1 - s_a) / V_a,
+// orthogonal under it, J0 is rho diag(1, V_a, V_a V_b, W_a),
+// W_a = s_a (1 - s_a) - k_a^2 V_a.  With M the change to that basis
+// J0^-1 = M^T diag^-1 M: some 60 operations, no factorisation.
+template <int D, typename E>
+struct QEInverse {
+    E u[3], k[3], sk[3], ir, iV[3], iW[3];  // sk = s - k u
+    __device__ QEInverse(E rho, const E (&u_)[3])
+    {
+        ir = rcp_(rho);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            u[a] = u_[a];
+            const E u2 = u[a] * u[a], sq = sqrt_(fma_(E(3), u2, E(1)));
+            const E s = E(1.0 / 3.0) + E(2) * u2 * rcp_(E(1) + sq), V = s - u2;
+            iV[a] = rcp_(V);
+            k[a] = u[a] * (E(1) - s) * iV[a];
+            iW[a] = rcp_(s * (E(1) - s) - k[a] * k[a] * V);
+            sk[a] = fma_(-k[a], u[a], s);
+        }
+    }
+    // out = J0^-1 r (r and out in the basis QEBasis)
+    template <typename R>
+    __device__ void operator()(R r, E (&out)[QEBasis<D>::K]) const
+    {
+        constexpr int SEC = 1 + D;  // second moments, a <= b
+        const E m0 = r(0);
+        E c0 = m0, c1[3] = {E(0), E(0), E(0)};
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            const E e = fma_(-u[a], m0, r(1 + a)) * iV[a];
+            c0 = fma_(-u[a], e, c0);
+            c1[a] = e;
+        }
+        int q = SEC;
+#pragma unroll
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+            for (int b = a; b < D; ++b, ++q) {
+                if (a == b) {
+                    // q_a = c_a^2 - k_a c_a - (s_a - k_a u_a)
+                    const E e = (r(q) - fma_(k[a], r(1 + a), sk[a] * m0)) * iW[a];
+                    out[q] = e * ir;
+                    c1[a] = fma_(-k[a], e, c1[a]);
+                    c0 = fma_(-sk[a], e, c0);
+                } else {
+                    const E e = (r(q) - fma_(u[a], r(1 + b), u[b] * fma_(-u[a], m0, r(1 + a)))) * (iV[a] * iV[b]);
+                    out[q] = e * ir;
+                    c1[a] = fma_(-u[b], e, c1[a]);
+                    c1[b] = fma_(-u[a], e, c1[b]);
+                    c0 = fma_(u[a] * u[b], e, c0);
+                }
+            }
+        out[0] = c0 * ir;
+#pragma unroll
+        for (int a = 0; a < D; ++a) out[1 + a] = c1[a] * ir;
+    }
+};
+
+// The solve near equilibrium.  delta starts from the exact first Newton step,
+// J0^-1 T; each further step is Newton's with the inverse of J = J0 + dJ, dJ_kl
+// = sum_i r_i phi_ik phi_il, as its Neumann series from J0^-1 to NT terms:
+//   s = sum_m (-J0^-1 dJ)^m (-J0^-1 F),
+// whose matrix entries are the moments the residual needs anyway.  With g the
+// measured ratio of successive terms a step leaves an error of about
+// (g^NT + |s|) |s|; converged when that is below tol.  Returns false where the
+// terms do not shrink (g above 0.3) or maxit steps do not do: the caller then
+// takes Newton's method with a factored Jacobian.
+template <typename E>
+struct QEFastCfg;
+template <>
+struct QEFastCfg<float> {
+    static constexpr int NT = 2, maxit = 6;
+    static constexpr float tol = 1e-9f;
+};
+template <>
+struct QEFastCfg<double> {
+    static constexpr int NT = 4, maxit = 6;
+    static constexpr double tol = 1e-17;
+};
+template <int D, typename E, typename FE>
+__device__ inline bool qe_fast(FE fe, const QEInverse<D, E> &inv, const E (&tgt)[QEBasis<D>::K],
+                               E (&delta)[QEBasis<D>::K], int &iters)
+{
+    using B = QEBasis<D>;
+    using C = QEFastCfg<E>;
+    constexpr int Q = Lat<D>::Q, K = B::K;
+    inv([&](int k) { return k <= D ? E(0) : tgt[k]; }, delta);
+    bool conv = false, ok = true;
+    int it = 1;
+    for (; it <= C::maxit && ok && !conv; ++it) {
+        E mr[Q];
+        qe_excess<D, E>(delta, fe, [&](int i, E r) { mr[i] = r; });
+        contract_rows<D, E>(mr);
+        E t[K], s[K];
+        inv([&](int k) { return tgt[k] - mr[B::m1(k)]; }, t);
+        E m0 = E(0), m1 = E(0), g = E(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            s[k] = t[k];
+            m0 = fmax_(m0, abs_(t[k]));
+        }
+#pragma unroll
+        for (int m = 1; m < C::NT; ++m) {
+            E y[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                E v = E(0);
+#pragma unroll
+                for (int l = 0; l < K; ++l) v = fma_(mr[B::m2(k, l)], t[l], v);
+                y[k] = -v;
+            }
+            inv([&](int k) { return y[k]; }, t);
+            m1 = E(0);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                s[k] += t[k];
+                m1 = fmax_(m1, abs_(t[k]));
+            }
+            if (m == 1) g = m1;
+        }
+        E mx = E(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            delta[k] += s[k];
+            mx = fmax_(mx, abs_(s[k]));
+        }
+        // (a NaN fails the comparisons: not ok, not converged)
+        ok = g <= E(0.3) * m0 && mx < E(0.25);
+        E gn = g * rcp_(fmax_(m0, E(1e-30)));
+        gn = C::NT == 2 ? gn * gn : (gn * gn) * (gn * gn);
+        conv = ok && (gn + mx) * mx <= C::tol;
+    }
+    iters = it - 1;
+    return conv;
+}
+
+// The solve by Newton's method from delta = 0 with the Jacobian factored, for
+// the cells qe_fast leaves (far from equilibrium).
+template <int D, typename E, typename FE>
+__device__ inline bool qe_newton(FE fe, const E (&tgt)[QEBasis<D>::K], E (&delta)[QEBasis<D>::K], int &iters)
 {
     using B = QEBasis<D>;
     constexpr int Q = Lat<D>::Q, K = B::K;
-    auto fe = [&](int i) { return E(gval<D, T, SH>(i, p)) + E(d[i]); };
-    // target T_k = c_Pr sigma_k = -c_Pr sum_i d_i phi_ik (second moments)
-    E tgt[K];
-    {
-        E md[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) md[i] = E(d[i]);
-        contract_rows<D, E>(md);
-#pragma unroll
-        for (int k = 0; k < K; ++k) tgt[k] = k <= D ? E(0) : -cpr * md[B::m1(k)];
-    }
     // moments of f^eq (single precision: they serve the Jacobian only)
     float mfe[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) mfe[i] = float(fe(i));
     contract_rows<D, float>(mfe);
 
-    E delta[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) delta[k] = E(0);
-    // true in every lane when every lane's exponents delta . phi_i are within
-    // the range of expm1_small (a wave-uniform choice, so that the wave takes
-    // one of the two forms)
-    auto small_exponents = [](const E (&dl)[K]) {
-        E bound = E(0);
-#pragma unroll
-        for (int k = 0; k < K; ++k) bound += abs_(dl[k]);
-        return __ballot(!(bound <= E(kSmallExpArg))) == 0ull;
-    };
     bool conv = false;
     int it = 0;
     for (; it < QECfg<E>::maxit && !conv; ++it) {
@@ -244,14 +387,7 @@ __device__ inline bool quasi_equilibrium(const T (&p)[Lat<D>::Q], T (&d)[Lat<D>:
 #pragma unroll
             for (int i = 0; i < Q; ++i) mr[i] = E(0);
         } else {
-            const QEArgs<D, E> qa(delta);
-            if (small_exponents(delta)) {
-#pragma unroll
-                for (int i = 0; i < Q; ++i) mr[i] = fe(i) * expm1_small(qa(i));
-            } else {
-#pragma unroll
-                for (int i = 0; i < Q; ++i) mr[i] = fe(i) * expm1_(qa(i));
-            }
+            qe_excess<D, E>(delta, fe, [&](int i, E r) { mr[i] = r; });
             contract_rows<D, E>(mr);
         }
         // Cholesky of J_kl = sum f^QE phi_k phi_l, packed lower triangle
@@ -301,15 +437,36 @@ __device__ inline bool quasi_equilibrium(const T (&p)[Lat<D>::Q], T (&d)[Lat<D>:
         conv = mx <= E(QECfg<E>::tol);
     }
     iters = it;
-    if (!conv) return false;
-    const QEArgs<D, E> qa(delta);
-    if (small_exponents(delta)) {
+    return conv;
+}
+
+// Replaces d = feq - g by f^QE - g.  p holds the stored values (g, or g - w
+// when SH), d the deviation of the equilibrium, rho and u its density and
+// velocity; E is the arithmetic type of the solve.  Returns false when Newton
+// does not converge (the target pressure lies beyond what positive
+// populations carry): d is then left as the equilibrium's.  iters receives
+// the Newton iterations.
+template <int D, typename T, typename E, bool SH>
+__device__ inline bool quasi_equilibrium(const T (&p)[Lat<D>::Q], T (&d)[Lat<D>::Q], E rho, const E (&u)[3], E cpr,
+                                         int &iters)
+{
+    using B = QEBasis<D>;
+    constexpr int Q = Lat<D>::Q, K = B::K;
+    auto fe = [&](int i) { return E(gval<D, T, SH>(i, p)) + E(d[i]); };
+    // target T_k = c_Pr sigma_k = -c_Pr sum_i d_i phi_ik (second moments)
+    E tgt[K], delta[K];
+    {
+        E md[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) d[i] = T(E(d[i]) + fe(i) * expm1_small(qa(i)));
-    } else {
+        for (int i = 0; i < Q; ++i) md[i] = E(d[i]);
+        contract_rows<D, E>(md);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) d[i] = T(E(d[i]) + fe(i) * expm1_(qa(i)));
+        for (int k = 0; k < K; ++k) tgt[k] = k <= D ? E(0) : -cpr * md[B::m1(k)];
     }
+    bool conv = qe_fast<D, E>(fe, QEInverse<D, E>(rho, u), tgt, delta, iters);
+    if (!conv) conv = qe_newton<D, E>(fe, tgt, delta, iters);
+    if (!conv) return false;
+    qe_excess<D, E>(delta, fe, [&](int i, E r) { d[i] = T(E(d[i]) + r); });
     conserve_moments<D, T>(d);
     return true;
 }

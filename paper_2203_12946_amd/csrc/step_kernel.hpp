@@ -535,7 +535,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             // path length is found from x = f^QE / g - 1 as before
             int qe_it = 0;
             bool qe_ok = true;
-            if constexpr (QE) qe_ok = quasi_equilibrium<D, T, EQ, SH>(p, dd, EQ(a.cpr), qe_it);
+            if constexpr (QE) {
+                const EQ rq = EQ(1) + EQ(drhoE), ir = rcp_(rq);
+                const EQ uq[3] = {EQ(jE[0]) * ir, EQ(jE[1]) * ir, D == 3 ? EQ(jE[2]) * ir : EQ(0)};
+                qe_ok = quasi_equilibrium<D, T, EQ, SH>(p, dd, rq, uq, EQ(a.cpr), qe_it);
+            }
             alpha = path_length<D, T, typename Pol::Exact, MODE, SH, typename Pol::Series>(pa, dd, a.beta, info);
             if constexpr (QE) {
                 info.iters = qe_it;
