@@ -25,8 +25,11 @@ namespace eselbm {
 //               568, 250x120x130 411 / 341; 16^3 6.8 / 7.2;
 //   D2Q9:       1500^2 66 / 63 (FP64), 33.5 / 30.9 (F32); 256^2 5.6 / 5.7,
 //               3.9 / 4.2; 1024^2 34.5 / 36.6, 16.7 / 16.6.
+//   cavities, D3Q27 F32: 192^3 308 / 288, 64^3 26.7 / 24.3, 128^3 101 / 110.
 // So planes where rows are ragged and the grid is beyond the smallest (whose
-// step is latency), and for the FP64 D3Q27 step below 256 cells a row.
+// step is latency), in D3Q27 also for rows of three waves (192 cells; not the
+// periodic F16-shifted step, 156 / 158) and the walled step's rows of one, and
+// for the FP64 D3Q27 step below 256 cells a row.
 static bool use_flat(int dtype, const StepArgs &a)
 {
     const Grid &g = a.g;
@@ -34,7 +37,8 @@ static bool use_flat(int dtype, const StepArgs &a)
     const bool ragged = g.nx % 64 != 0 || (g.nx > 256 && g.nx % 256 != 0);
     if (g.D == 2) return ragged && g.N >= 1 << 18;
     if (dtype == 0) return (ragged || g.nx < 256) && g.N >= 1 << 15;
-    return ragged && g.N >= 1 << 16;
+    const bool three = g.nx == 192 && (dtype != 2 || a.walls || a.cpr != 0.0);
+    return (ragged || three || (a.walls && g.nx == 64)) && g.N >= 1 << 16;
 }
 
 hipError_t launch_step(int dtype, int mode, bool diag, const StepArgs &a, hipStream_t s)

@@ -548,8 +548,9 @@ struct ExtendedCfg<double> {
 };
 // Taylor coefficients (exact rationals) of 2/(2+x) and of the fraction of c
 // over x^2, for x^0.., and of R(y)
-constexpr double kC1[13] = {1.0, -0.5, 0.25, -1.0 / 8.0, 1.0 / 16.0, -1.0 / 32.0, 1.0 / 64.0, -1.0 / 128.0,
-                            1.0 / 256.0, -1.0 / 512.0, 1.0 / 1024.0, -1.0 / 2048.0, 1.0 / 4096.0};
+constexpr double kC1[17] = {1.0, -0.5, 0.25, -1.0 / 8.0, 1.0 / 16.0, -1.0 / 32.0, 1.0 / 64.0, -1.0 / 128.0,
+                            1.0 / 256.0, -1.0 / 512.0, 1.0 / 1024.0, -1.0 / 2048.0, 1.0 / 4096.0,
+                            -1.0 / 8192.0, 1.0 / 16384.0, -1.0 / 32768.0, 1.0 / 65536.0};
 constexpr double kC[13] = {1.0, -0.5, 1.0 / 3.0, -0.25, 1.0 / 5.0, -1.0 / 6.0, 57.0 / 400.0, -99.0 / 800.0,
                            2603.0 / 24000.0, -1529.0 / 16000.0, 13513.0 / 160000.0, -71779.0 / 960000.0,
                            212029.0 / 3200000.0};
@@ -563,7 +564,7 @@ constexpr double kR[12] = {1.25, -5.0 / 8.0, 3.0 / 8.0, -0.25, 45.0 / 256.0, -65
 //           (|T_7| <= X^5 T_2, entering dH as (a^7/42 - a/6) T_7);
 //   double, X = 0.005, K = 8: under 6e-16 (X^7 T_2 times a^9/72 - a/8).
 // Beyond X, the extended moments:
-//   float,  X = 0.08, K = 10: 2.5e-9;   double, X = 0.03, K = 12: 1e-15.
+//   float,  X = 0.18, K = 14: 4e-8;   double, X = 0.08, K = 18: 4e-16.
 template <typename T>
 struct MirrorSeriesCfg;
 template <>
@@ -580,13 +581,13 @@ template <typename T>
 struct MirrorExtendedCfg;
 template <>
 struct MirrorExtendedCfg<float> {
-    static constexpr int K = 10;
-    static constexpr double X = 0.08;
+    static constexpr int K = 14;
+    static constexpr double X = 0.18;
 };
 template <>
 struct MirrorExtendedCfg<double> {
-    static constexpr int K = 12;
-    static constexpr double X = 0.03;
+    static constexpr int K = 18;
+    static constexpr double X = 0.08;
 };
 
 template <typename T>
@@ -660,6 +661,15 @@ __device__ __attribute__((always_inline)) inline A alpha_exact(const P &p, const
     constexpr int Q = Lat<D>::Q;
     A S2 = 0, M3 = 0, M4 = 0, M5 = 0, M6 = 0, C1 = 0, C = 0;
     xmin = A(0);
+    // the polynomials with leading coefficient one, their factors taken out of
+    // the sums, and their other coefficients in scalar registers: one operand
+    // of each multiply-add (as literals a double takes two moves each)
+    auto scalar = [](double v) {
+        A c = A(v);
+        asm("" : "+s"(c));
+        return c;
+    };
+    const A k12 = scalar(12.0), k30 = scalar(30.0), k20 = scalar(20.0), kn = scalar(60.0 / 11.0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         // the population is read here, and its terms are added to the sums
@@ -682,19 +692,22 @@ __device__ __attribute__((always_inline)) inline A alpha_exact(const P &p, const
         M5 += v;
         M6 += v * xn;
         const A q1 = A(2) + xi;
-        const A p3 = A(60) + xi * (A(90) + xi * (A(36) + A(3) * xi));
+        const A p3 = fma_(xi, fma_(xi, xi + k12, k30), k20);  // a third of 60 + 90 x + 36 x^2 + 3 x^3
         const A r = rcp_(q1 * p3);
-        C1 += A(2) * gx2 * p3 * r;
-        C += gx2 * (A(60) + xi * (A(60) + A(11) * xi)) * q1 * r;
+        C1 = fma_(gx2 * p3, r, C1);
+        C = fma_(gx2 * fma_(xi, xi + kn, kn), q1 * r, C);
         asm volatile("" : "+v"(S2), "+v"(M3), "+v"(M4), "+v"(M5), "+v"(M6), "+v"(C1), "+v"(C), "+v"(xmin));
         // one population at a time: interleaving the unrolled iterations
         // would hold more temporaries than the register budget
         __builtin_amdgcn_sched_barrier(0);
     }
+    C1 *= A(2);
+    C *= A(11.0 / 3.0);
     const A b1 = A(0.5) * S2;
     const A aL = conj_root(A(0.5) * M3, b1, C1);
     if (MODE == MODE_LOWER) return aL;
     A Bp = A(0);
+    const A kr = scalar(80.0 / 19.0), ks = scalar(22.0 / 3.0), kt = scalar(32.0 / 3.0), k16 = scalar(16.0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         // x again, from d and g (not the first loop's Q values of x, which
@@ -704,13 +717,13 @@ __device__ __attribute__((always_inline)) inline A alpha_exact(const P &p, const
         const A dp = fmax_(A(di), A(0));
         const A xp = dp * rcp_(A(gi));  // x on Omega+, else 0
         const A y = aL * xp;
-        const A num = A(80) + y * (A(80) + A(19) * y);
-        const A den = A(64) + y * (A(96) + y * (A(44) + A(6) * y));
-        Bp += dp * xp * xp * num * rcp_(den);  // g x^3 R(aL x) on Omega+, else 0
+        const A num = fma_(y, y + kr, kr);
+        const A den = fma_(y, fma_(y, y + ks, k16), kt);
+        Bp = fma_(dp * xp * xp * num, rcp_(den), Bp);  // g x^3 R(aL x) on Omega+, else 0
         asm volatile("" : "+v"(Bp));
         __builtin_amdgcn_sched_barrier(0);
     }
-    return higher_from_coeffs(aL, b1, Bp, C, M3, M4, M5, M6, beta);
+    return higher_from_coeffs(aL, b1, A(19.0 / 6.0) * Bp, C, M3, M4, M5, M6, beta);
 }
 
 // alpha_Lower, and alpha_Higher from it, through the Taylor series of the
@@ -897,8 +910,8 @@ __device__ __attribute__((always_inline)) inline A mirror_newton(DH dH, A aL, A 
 // difference of two sums.  With this, the extended moments and the row-wise
 // passes of mirror_alpha the modes run at the plain step's registers and occupancy
 // (F32 D3Q27: 256 -> 121 VGPRs, two -> four waves per SIMD).  150x150x120,
-// per step, in a developed near-inviscid vortex: ELBM 307 -> 204 us (F32),
-// 591 -> 338 us (FP64); one Newton step 264 -> 189 us (F32).
+// per step, in a developed near-inviscid vortex: ELBM 306 -> 164 us (F32),
+// 598 -> 301 us (FP64); one Newton step 264 -> 189 us (F32).
 template <typename T, bool FULL, int K>
 __device__ __attribute__((always_inline)) inline T mirror_series(const T *Tm, T aL, T xmin, CellInfo &info)
 {
