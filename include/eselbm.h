@@ -39,9 +39,9 @@
  * Ownership: every buffer passed in is device memory owned by the caller.
  * The library never frees caller memory.  It owns only the handle, a
  * small (under 10 KiB) device block of diagnostic accumulators and the wall
- * table, which eselbm_create allocates, the losses' scratch (allocated by
- * the first loss call) and 8 KiB of pinned host memory (by the first
- * eselbm_alpha_stats), all of which eselbm_destroy frees.  Besides, each
+ * table and 8 KiB of pinned host memory, which eselbm_create allocates, and
+ * the losses' scratch (allocated by the first loss call), all of which
+ * eselbm_destroy frees.  Besides, each
  * device the library runs on holds one fixed 512 KiB array of partial sums
  * for eselbm_kinetic_loss_noalloc until the process ends (it is part of the
  * loaded code, not allocated by any call).

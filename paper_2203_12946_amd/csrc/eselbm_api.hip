@@ -21,7 +21,7 @@ struct eselbm_ctx {
     int stats_on;
     int have_stats;
     int h_added;           // an H pass has added to the slots since the last reset
-    DevStats *host_stats;  // pinned, kStatSlots slots: where alpha_stats reads them back (first use allocates)
+    DevStats *host_stats;  // pinned, kStatSlots slots: where alpha_stats reads them back (or null)
     int device;
     void *alpha_field;
     void *nut_field;
@@ -108,11 +108,19 @@ eselbm_status eselbm_create(eselbm_handle *out, int lattice, int nx, int ny, int
         return hip_fail(e, "eselbm_create: hipMalloc");
     }
     h->wall_eq = (double *)(h->dev_stats + kStatSlots);
+    // 8 KiB of pinned memory for the statistics' read-back (here, where device
+    // memory is allocated too, not at the first read-back; without it that
+    // goes through pageable memory)
+    if (hipHostMalloc((void **)&h->host_stats, sizeof(DevStats) * kStatSlots, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->host_stats = nullptr;
+    }
     // the device address of the allocation-free kinetic loss's fixed array,
     // looked up once per device (this device is current here)
     e = noalloc_scratch(h->device, &h->noalloc_parts);
     if (e != hipSuccess) {
         hipFree(h->dev_stats);
+        if (h->host_stats) hipHostFree(h->host_stats);
         delete h;
         return hip_fail(e, "eselbm_create: device address of the fixed loss buffer");
     }
@@ -341,17 +349,12 @@ eselbm_status eselbm_alpha_stats(eselbm_handle h, eselbm_stats *out, int with_H,
         if (e != hipSuccess) return hip_fail(e, "eselbm_alpha_stats: H launch");
         h->h_added = 1;
     }
-    // pinned: a read-back into pageable memory is staged by the runtime
-    // (64^2 FP64, a step, its statistics and H: 43.4 us, now 32.7)
-    if (!h->host_stats) {
-        hipError_t e = hipHostMalloc((void **)&h->host_stats, sizeof(DevStats) * kStatSlots, hipHostMallocDefault);
-        if (e != hipSuccess) {
-            h->host_stats = nullptr;
-            return hip_fail(e, "eselbm_alpha_stats: hipHostMalloc");
-        }
-    }
-    const DevStats *host = h->host_stats;
-    hipError_t e = hipMemcpyAsync(h->host_stats, h->dev_stats, sizeof(DevStats) * kStatSlots, hipMemcpyDeviceToHost, s);
+    // into the handle's pinned block (pageable memory is staged by the runtime:
+    // 64^2 FP64, a step, its statistics and H 43.4 us, now 32.7), or onto the
+    // stack if the handle could not have one
+    DevStats stack[kStatSlots];
+    DevStats *host = h->host_stats ? h->host_stats : stack;
+    hipError_t e = hipMemcpyAsync(host, h->dev_stats, sizeof(DevStats) * kStatSlots, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "eselbm_alpha_stats: read-back");
     std::memset(out, 0, sizeof(*out));
