@@ -350,14 +350,20 @@ __device__ inline bool qe_fast(FE fe, const QEInverse<D, E> &inv, const E (&tgt)
             delta[k] += s[k];
             mx = fmax_(mx, abs_(s[k]));
         }
-        // (a NaN fails the comparisons: not ok, not converged)
         ok = g <= E(0.3) * m0 && mx < E(0.25);
         E gn = g * rcp_(fmax_(m0, E(1e-30)));
         gn = C::NT == 2 ? gn * gn : (gn * gn) * (gn * gn);
         conv = ok && (gn + mx) * mx <= C::tol;
     }
+    // The maxima drop a NaN: where the moments of overflowing exponentials
+    // left one in the step, it shows in the sum of the multipliers, which the
+    // caller's choice of the exponential's form takes anyway.  The bound on a
+    // multiplier is that of qe_newton's steps.
+    E sum = E(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) sum += abs_(delta[k]);
     iters = it - 1;
-    return conv;
+    return conv && sum < E(1e3);
 }
 
 // The solve by Newton's method from delta = 0 with the Jacobian factored, for
