@@ -20,7 +20,7 @@ struct eselbm_ctx {
     int mode;
     int stats_on;
     int have_stats;
-    int h_added;           // an H pass has added to the slots since the last reset
+    int h_clear;           // the slots' H is zero: a reset has run, and no H pass since
     DevStats *host_stats;  // pinned, kStatSlots slots: where alpha_stats reads them back (or null)
     int device;
     void *alpha_field;
@@ -317,7 +317,10 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         if (sa.stats) {
             hipError_t e = launch_reset_stats(h->dev_stats, s);
             if (e != hipSuccess) return hip_fail(e, "eselbm_step: reset");
-            h->h_added = 0;
+            // a reset that a graph captures has not run
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+            if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+            else if (cap == hipStreamCaptureStatusNone) h->h_clear = 1;
         }
         hipError_t e = launch_step(h->dtype, h->mode, diag, sa, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_step: launch");
@@ -345,9 +348,9 @@ eselbm_status eselbm_alpha_stats(eselbm_handle h, eselbm_stats *out, int with_H,
     if (eselbm_status st = device_check(h, "eselbm_alpha_stats")) return st;
     hipStream_t s = (hipStream_t)stream;
     if (with_H) {
-        hipError_t e = launch_H(h->dtype, h->g, h->last_out, h->dev_stats, h->h_added != 0, s);
+        hipError_t e = launch_H(h->dtype, h->g, h->last_out, h->dev_stats, !h->h_clear, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_alpha_stats: H launch");
-        h->h_added = 1;
+        h->h_clear = 0;
     }
     // into the handle's pinned block (pageable memory is staged by the runtime:
     // 64^2 FP64, a step, its statistics and H 43.4 us, now 32.7), or onto the

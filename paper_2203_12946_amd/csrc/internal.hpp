@@ -65,7 +65,7 @@ hipError_t launch_init_eq(int dtype, const Grid &g, const double *rho, const dou
                           hipStream_t s);
 hipError_t launch_moments(int dtype, const Grid &g, const void *f, const float *force, double *rho,
                           double *u, hipStream_t s);
-// (zero: clears the slots' H first; a step's reset has cleared it once)
+// (zero: clears the slots' H first, needed unless a reset is all that ran on them)
 hipError_t launch_H(int dtype, const Grid &g, const void *f, DevStats *st, bool zero, hipStream_t s);
 
 struct AdjArgs {
