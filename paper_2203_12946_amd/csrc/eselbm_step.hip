@@ -199,9 +199,10 @@ __device__ inline double H_cell(const S (&f)[Lat<D>::Q])
     };
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        // (false for a non-positive or NaN population)
+        // |z| <= 0.375 as bounds on v: false for a non-positive, infinite or NaN
+        // population, and for a double beyond the range of float
         const float w = (float)Lat<D>::w(i), t = (float)Storage<S>::to_T(f[i]), v = SH ? w + t : t;
-        near = near && abs_(v - w) <= 0.375f * (v + w);
+        near = near && v >= float(5.0 / 11.0) * w && v <= 2.2f * w;
     }
     if (__ballot(!near) == 0ull) {
 #pragma unroll
