@@ -26,17 +26,25 @@ __device__ inline V wave_sum(V v)
     return v;
 }
 
-// min and max over the wave of positive doubles (path lengths)
-__device__ inline double wave_min(double v)
+// min and max over the wave of the bits of doubles, as unsigned numbers: the
+// order of positive doubles, with a NaN beyond them (a floating-point maximum
+// would drop it)
+__device__ inline unsigned long long wave_min(unsigned long long v)
 {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = __builtin_fmin(v, __shfl_xor(v, o, 64));
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long t = __shfl_xor(v, o, 64);
+        v = t < v ? t : v;
+    }
     return v;
 }
-__device__ inline double wave_max(double v)
+__device__ inline unsigned long long wave_max(unsigned long long v)
 {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = __builtin_fmax(v, __shfl_xor(v, o, 64));
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long t = __shfl_xor(v, o, 64);
+        v = t > v ? t : v;
+    }
     return v;
 }
 
@@ -44,7 +52,7 @@ __device__ inline double wave_max(double v)
 // one accumulator slot with one atomic per quantity per block.
 struct LaneStats {
     double mass = 0, mom[3] = {0, 0, 0}, ke = 0, asum = 0;
-    double amin = __builtin_inf(), amax = 0;  // of the cells that collided
+    unsigned long long amin = 0x7FF0000000000000ull, amax = 0;  // bits, of the cells that collided
     bool n = false, gated = false, guard = false, nonpos = false, lt2 = false, exact = false, fallback = false;
     int iters = 0;
 };
@@ -56,22 +64,22 @@ template <bool ITER>
 __device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot)
 {
     constexpr int NU = 8;  // counters
-    __shared__ double red_d[4][8];
-    __shared__ unsigned long long red_u[4][NU];
+    __shared__ double red_d[4][6];
+    __shared__ unsigned long long red_u[4][NU + 2];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     double v[6] = {s.mass, s.mom[0], s.mom[1], s.mom[2], s.ke, s.asum};
 #pragma unroll
     for (int k = 0; k < 6; ++k) v[k] = wave_sum(v[k]);
-    const double mn = wave_min(s.amin), mx = wave_max(s.amax);
+    const unsigned long long mn = wave_min(s.amin), mx = wave_max(s.amax);
     auto count = [](bool c) { return (unsigned long long)__popcll(__ballot(c)); };
     const unsigned long long c[NU] = {count(s.n), count(s.gated), count(s.guard), count(s.nonpos), count(s.lt2),
                                       count(s.exact), ITER ? (unsigned long long)wave_sum(s.iters) : 0ull,
                                       ITER ? count(s.fallback) : 0ull};
     if (lane == 0) {
         for (int k = 0; k < 6; ++k) red_d[wid][k] = v[k];
-        red_d[wid][6] = mn;
-        red_d[wid][7] = mx;
         for (int k = 0; k < NU; ++k) red_u[wid][k] = c[k];
+        red_u[wid][NU] = mn;
+        red_u[wid][NU + 1] = mx;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -79,12 +87,12 @@ __device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot)
         DevStats *st = slot;
         double t[6] = {0, 0, 0, 0, 0, 0};
         unsigned long long u[NU] = {0, 0, 0, 0, 0, 0, 0, 0};
-        double tmn = red_d[0][6], tmx = red_d[0][7];
+        unsigned long long tmn = red_u[0][NU], tmx = red_u[0][NU + 1];
         for (int w = 0; w < nw; ++w) {
             for (int k = 0; k < 6; ++k) t[k] += red_d[w][k];
             for (int k = 0; k < NU; ++k) u[k] += red_u[w][k];
-            tmn = __builtin_fmin(tmn, red_d[w][6]);
-            tmx = __builtin_fmax(tmx, red_d[w][7]);
+            tmn = red_u[w][NU] < tmn ? red_u[w][NU] : tmn;
+            tmx = red_u[w][NU + 1] > tmx ? red_u[w][NU + 1] : tmx;
         }
         atomicAdd(&st->mass, t[0]);
         atomicAdd(&st->mom[0], t[1]);
@@ -100,9 +108,8 @@ __device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot)
         if (u[5]) atomicAdd(&st->n_exact, u[5]);
         if (u[6]) atomicAdd(&st->n_iter, u[6]);
         if (u[7]) atomicAdd(&st->n_fallback, u[7]);
-        // (positive doubles order as their bits)
-        atomicMin(&st->alpha_min_bits, (unsigned long long)__double_as_longlong(tmn));
-        atomicMax(&st->alpha_max_bits, (unsigned long long)__double_as_longlong(tmx));
+        atomicMin(&st->alpha_min_bits, tmn);
+        atomicMax(&st->alpha_max_bits, tmx);
     }
 }
 
@@ -644,7 +651,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
                 }
                 ls.ke = 0.5 * jj / r;
                 ls.asum = (double)alpha;
-                ls.amin = ls.amax = (double)alpha;
+                ls.amin = ls.amax = (unsigned long long)__double_as_longlong((double)alpha);
                 ls.n = true;
                 ls.gated = info.gated;
                 ls.guard = info.guarded;

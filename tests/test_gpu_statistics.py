@@ -131,3 +131,22 @@ def test_H_on_both_sides_of_the_series_in_one_wave(es):
             terms = f * (np.log(f / w) - 1)
             # each term to a few roundings, summed in FP64
             assert abs(s.stats(with_H=True)["H"] - np.sum(terms)) <= 1e-13 * np.sum(np.abs(terms)), (dtype, band)
+
+
+@pytest.mark.parametrize("mode", ["higher", "lower"])
+def test_a_NaN_path_length_shows(es, mode):
+    """A cell with strictly positive populations, one of them so small that its
+    path length overflows to NaN, among healthy cells: alpha_max is NaN and
+    alpha_min that of the others."""
+    s, a = _state(es, 2, (6, 70), "f64")
+    s.set_mode(mode)
+    b, alpha = s.empty_state(), torch.empty((6, 70), dtype=torch.float64, device="cuda")
+    a[4, 3, 33] = 1e-320  # the rest population, which does not move
+    s.set_alpha_field(alpha)
+    s.set_stats(True)
+    s.step(a, b, 1, 0.1)
+    st = s.stats()
+    al = alpha.cpu().numpy()
+    assert st["n_nonpos"] == 0 and np.isnan(al).sum() == 1 and np.isnan(al[3, 33])
+    assert np.isnan(st["alpha_max"]) and np.isnan(st["alpha_mean"])
+    assert st["alpha_min"] == np.nanmin(al)
