@@ -3,7 +3,8 @@
  * rollout makes them, for callers whose own loop costs more than the kernels
  * it launches (a small lattice steps in a few microseconds).  Each function
  * makes the calls named here, in this order and with these arguments, and
- * returns the first status that is not ESELBM_OK.
+ * returns the first status that is not ESELBM_OK; the arguments of all of
+ * them are checked before the first is made.
  */
 #ifndef ESELBM_ROLLOUT_H
 #define ESELBM_ROLLOUT_H

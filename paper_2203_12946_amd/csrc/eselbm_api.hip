@@ -252,7 +252,16 @@ eselbm_status eselbm_init_equilibrium(eselbm_handle h, const double *rho, const 
     return ESELBM_OK;
 }
 
-eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, double tau, void *stream)
+// ES-BGK: c_Pr = (1 - 1/Pr) / (1 + 1/(2 tau1 Pr)), tau1 = tau; 0: none
+static double stress_factor(eselbm_handle h, double tau)
+{
+    return h->prandtl == 1.0 ? 0.0 : (1.0 - 1.0 / h->prandtl) / (1.0 + 1.0 / (2.0 * tau * h->prandtl));
+}
+
+static size_t state_bytes(eselbm_handle h) { return (size_t)h->g.Q * (size_t)h->g.N * elem_size(h->dtype); }
+
+// eselbm_step's arguments
+static eselbm_status step_check(eselbm_handle h, const void *f_in, const void *f_out, int nsteps, double tau)
 {
     if (!h) return fail(ESELBM_E_ARG, "eselbm_step: NULL handle");
     if (!f_in || !f_out) return fail(ESELBM_E_ARG, "eselbm_step: NULL state buffer");
@@ -260,14 +269,13 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
     if (nsteps < 1) return fail(ESELBM_E_ARG, "eselbm_step: nsteps must be >= 1");
     if (h->force && h->mode == ESELBM_MODE_LBGK) return fail(ESELBM_E_UNSUPPORTED, "eselbm_step: forcing in the classic LBGK mode");
     if (!(tau > 0.0) || !std::isfinite(tau)) return fail(ESELBM_E_ARG, "eselbm_step: tau must be finite and > 0");
-    // ES-BGK: c_Pr = (1 - 1/Pr) / (1 + 1/(2 tau1 Pr)), tau1 = tau
-    const double cpr = h->prandtl == 1.0 ? 0.0 : (1.0 - 1.0 / h->prandtl) / (1.0 + 1.0 / (2.0 * tau * h->prandtl));
+    const double cpr = stress_factor(h, tau);
     if (cpr != 0.0) {
         if (h->mode != ESELBM_MODE_HIGHER && h->mode != ESELBM_MODE_LOWER && h->mode != ESELBM_MODE_BGK)
             return fail(ESELBM_E_UNSUPPORTED, "eselbm_step: ES-BGK takes the modes HIGHER, LOWER and BGK");
         if (h->force || h->walls) return fail(ESELBM_E_UNSUPPORTED, "eselbm_step: ES-BGK is periodic and unforced");
     }
-    const size_t bytes = (size_t)h->g.Q * (size_t)h->g.N * elem_size(h->dtype);
+    const size_t bytes = state_bytes(h);
     const char *a = (const char *)f_in, *b = (const char *)f_out;
     const bool in_place = f_in == f_out;
     if (!in_place && a < b + bytes && b < a + bytes) return fail(ESELBM_E_ARG, "eselbm_step: f_in and f_out overlap");
@@ -278,6 +286,14 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
             h->mode != ESELBM_MODE_LBGK)
             return fail(ESELBM_E_UNSUPPORTED, "eselbm_step: in-place stepping takes the modes HIGHER, LOWER, BGK and LBGK");
     }
+    return ESELBM_OK;
+}
+
+eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, double tau, void *stream)
+{
+    if (eselbm_status st = step_check(h, f_in, f_out, nsteps, tau)) return st;
+    const double cpr = stress_factor(h, tau);
+    const bool in_place = f_in == f_out;
     hipStream_t s = (hipStream_t)stream;
     // Step k reads one buffer and writes the other, starting f_in -> f_out;
     // after an even count the newest state is back in f_in.  In place
@@ -331,7 +347,7 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         }
     }
     if (src != f_out && !pair) {
-        hipError_t e = hipMemcpyAsync(f_out, src, bytes, hipMemcpyDeviceToDevice, s);
+        hipError_t e = hipMemcpyAsync(f_out, src, state_bytes(h), hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_step: copy");
     }
     if (h->stats_on) {
@@ -401,12 +417,9 @@ eselbm_status eselbm_moments(eselbm_handle h, const void *f, double *rho, double
     return ESELBM_OK;
 }
 
-// The adjoint step behind both entry points: the loss seed of the state
-// after the step, if any, comes as a compact seed (seed_next) or as that
-// state's velocity field (seed_uv), whose dissipation seed the kernel forms.
-static eselbm_status adjoint_step_impl(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
-                                       const float *seed_uv, double seed_w, void *lam_n, double tau, void *force_grad,
-                                       void *stream, const char *who)
+// The arguments of the adjoint steps, and those of eselbm_adjoint_step_diss alone
+static eselbm_status adjoint_check(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
+                                   const void *lam_n, double tau, const void *force_grad, const char *who)
 {
     if (!h || !f_n || !lam_next || !lam_n) return fail(ESELBM_E_ARG, std::string(who) + ": NULL argument");
     if (eselbm_status st = device_check(h, who)) return st;
@@ -419,6 +432,26 @@ static eselbm_status adjoint_step_impl(eselbm_handle h, const void *f_n, const v
         return fail(ESELBM_E_UNSUPPORTED, std::string(who) + ": no adjoint of the ELBM, Iterate1 and classic LBGK modes");
     if (h->walls) return fail(ESELBM_E_UNSUPPORTED, std::string(who) + ": the adjoint is periodic only");
     if (h->prandtl != 1.0) return fail(ESELBM_E_UNSUPPORTED, std::string(who) + ": no adjoint of the ES-BGK collision");
+    return ESELBM_OK;
+}
+static eselbm_status adjoint_diss_check(eselbm_handle h, const float *uv_next, double weight, const void *lam_n)
+{
+    if (!h || !uv_next) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: NULL argument");
+    if (!std::isfinite(weight)) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: weight must be finite");
+    if (h->dtype != ESELBM_F32 && h->dtype != ESELBM_F32_SHIFTED)
+        return fail(ESELBM_E_UNSUPPORTED, "eselbm_adjoint_step_diss: single-precision adjoints only (F32, F32-shifted)");
+    if (uv_next == (const float *)lam_n) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: lam_n must not alias uv_next");
+    return ESELBM_OK;
+}
+
+// The adjoint step behind both entry points: the loss seed of the state
+// after the step, if any, comes as a compact seed (seed_next) or as that
+// state's velocity field (seed_uv), whose dissipation seed the kernel forms.
+static eselbm_status adjoint_step_impl(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
+                                       const float *seed_uv, double seed_w, void *lam_n, double tau, void *force_grad,
+                                       void *stream, const char *who)
+{
+    if (eselbm_status st = adjoint_check(h, f_n, lam_next, seed_next, lam_n, tau, force_grad, who)) return st;
     AdjArgs a;
     a.fn = f_n;
     a.lam_next = lam_next;
@@ -445,11 +478,7 @@ eselbm_status eselbm_adjoint_step(eselbm_handle h, const void *f_n, const void *
 eselbm_status eselbm_adjoint_step_diss(eselbm_handle h, const void *f_n, const void *lam_next, const float *uv_next,
                                        double weight, void *lam_n, double tau, void *force_grad, void *stream)
 {
-    if (!h || !uv_next) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: NULL argument");
-    if (!std::isfinite(weight)) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: weight must be finite");
-    if (h->dtype != ESELBM_F32 && h->dtype != ESELBM_F32_SHIFTED)
-        return fail(ESELBM_E_UNSUPPORTED, "eselbm_adjoint_step_diss: single-precision adjoints only (F32, F32-shifted)");
-    if (uv_next == (const float *)lam_n) return fail(ESELBM_E_ARG, "eselbm_adjoint_step_diss: lam_n must not alias uv_next");
+    if (eselbm_status st = adjoint_diss_check(h, uv_next, weight, lam_n)) return st;
     return adjoint_step_impl(h, f_n, lam_next, nullptr, uv_next, weight, lam_n, tau, force_grad, stream,
                              "eselbm_adjoint_step_diss");
 }
@@ -509,8 +538,7 @@ eselbm_status eselbm_dissipation_seed(eselbm_handle h, const void *f, void *seed
     return ESELBM_OK;
 }
 
-eselbm_status eselbm_dissipation_loss_uv(eselbm_handle h, const float *uv, double *loss_dev, void *lam, void *seed,
-                                         double weight, void *force_grad, void *stream)
+static eselbm_status loss_uv_check(eselbm_handle h, const float *uv, const void *lam, const void *seed, const void *force_grad)
 {
     if (!h || !uv) return fail(ESELBM_E_ARG, "eselbm_dissipation_loss_uv: NULL argument");
     if (eselbm_status st = device_check(h, "eselbm_dissipation_loss_uv")) return st;
@@ -518,6 +546,13 @@ eselbm_status eselbm_dissipation_loss_uv(eselbm_handle h, const float *uv, doubl
     if (force_grad && !h->force) return fail(ESELBM_E_ARG, "eselbm_dissipation_loss_uv: force_grad without a registered force");
     if (lam && seed) return fail(ESELBM_E_ARG, "eselbm_dissipation_loss_uv: give lam or seed, not both");
     if (h->walls) return fail(ESELBM_E_UNSUPPORTED, "eselbm_dissipation_loss_uv: periodic differences only");
+    return ESELBM_OK;
+}
+
+eselbm_status eselbm_dissipation_loss_uv(eselbm_handle h, const float *uv, double *loss_dev, void *lam, void *seed,
+                                         double weight, void *force_grad, void *stream)
+{
+    if (eselbm_status st = loss_uv_check(h, uv, lam, seed, force_grad)) return st;
     hipError_t e = launch_dissipation_loss(h->loss_scratch, h->dtype, h->g, nullptr, uv, h->force, loss_dev, lam, seed,
                                            weight, (float *)force_grad, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "eselbm_dissipation_loss_uv: launch");
@@ -541,12 +576,20 @@ eselbm_status eselbm_rollout_steps(eselbm_handle h, const void *f, void *const *
     if (!h || !f || !states) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: NULL argument");
     if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: n must be >= 1");
     if (loss_dev && !uvs) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: the loss needs velocity fields");
-    eselbm_status st = ESELBM_OK;
+    // every call's arguments before the first is made
     void *src = const_cast<void *>(f);  // one step at a time: eselbm_step does not write its input
+    for (int k = 0; k < n; ++k) {
+        if (states[k] == src) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: a step onto its own input");
+        if (eselbm_status st = step_check(h, src, states[k], 1, tau)) return st;
+        if (loss_dev)
+            if (eselbm_status st = loss_uv_check(h, uvs[k], nullptr, nullptr, nullptr)) return st;
+        src = states[k];
+    }
+    eselbm_status st = ESELBM_OK;
+    src = const_cast<void *>(f);
     for (int k = 0; k < n && st == ESELBM_OK; ++k) {
         if (uvs) h->uv_field = uvs[k];
-        st = states[k] == src ? fail(ESELBM_E_ARG, "eselbm_rollout_steps: a step onto its own input")
-                              : eselbm_step(h, src, states[k], 1, tau, stream);
+        st = eselbm_step(h, src, states[k], 1, tau, stream);
         if (st == ESELBM_OK && loss_dev)
             st = eselbm_dissipation_loss_uv(h, uvs[k], loss_dev, nullptr, nullptr, weight, nullptr, stream);
         src = states[k];
@@ -561,6 +604,16 @@ eselbm_status eselbm_rollout_adjoints(eselbm_handle h, const void *const *states
 {
     if (!h || !states || !lam || !other) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: NULL argument");
     if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: n must be >= 1");
+    // every call's arguments before the first is made
+    for (int k = 0; k < n; ++k) {
+        const void *from = k % 2 ? other : lam, *to = k % 2 ? lam : other;
+        const bool diss = uvs && uvs[k];
+        if (diss)
+            if (eselbm_status st = adjoint_diss_check(h, uvs[k], weight, to)) return st;
+        if (eselbm_status st = adjoint_check(h, states[k], from, nullptr, to, tau, force_grad,
+                                             diss ? "eselbm_adjoint_step_diss" : "eselbm_adjoint_step"))
+            return st;
+    }
     eselbm_status st = ESELBM_OK;
     for (int k = 0; k < n && st == ESELBM_OK; ++k) {
         st = uvs && uvs[k] ? eselbm_adjoint_step_diss(h, states[k], lam, uvs[k], weight, other, tau, force_grad, stream)

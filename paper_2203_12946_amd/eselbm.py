@@ -322,13 +322,13 @@ class Solver:
             self._p(t, self.storage_dtype, n)
         for t in uvs or ():
             self._p(t, torch.float32, (self.D + 1) * self.cells)
-        if uvs is not None:
-            self._uv = None
         with self._on():
             _check(lib.eselbm_rollout_steps(
                 self._h, self._p(f, self.storage_dtype, n), self._pointers(outs),
                 None if uvs is None else self._pointers(uvs), len(outs), float(tau), self._p(loss, torch.float64, 1),
                 float(weight), _stream(stream)))
+        if uvs is not None:
+            self._uv = None  # (after an argument error the registered field stays)
 
     def adjoint_series(self, states, lam, other, tau: float, uvs=None, weight: float = 0.0, force_grad=None,
                        stream=None):
