@@ -40,6 +40,19 @@ import torch
 
 from .eselbm import Solver
 
+# the calls that the solver's native sequences make in place of these methods
+_SEQUENCE_CALLS = {
+    "step_series": {m: getattr(Solver, m) for m in ("step", "set_velocity_field", "dissipation_loss_uv")},
+    "adjoint_series": {m: getattr(Solver, m) for m in ("adjoint_step", "adjoint_step_diss")},
+}
+
+
+def _native(solver, series: str) -> bool:
+    """Whether the solver has the native sequence and the methods it stands
+    for are Solver's own, not a subclass's or an instance's."""
+    return hasattr(solver, series) and all(
+        getattr(getattr(solver, m), "__func__", None) is f for m, f in _SEQUENCE_CALLS[series].items())
+
 
 class Rollout:
     def __init__(self, solver: Solver, tau: float, nsteps: int, ckpt_every: int,
@@ -74,7 +87,7 @@ class Rollout:
         s = self.s
         if not outs:
             return
-        if hasattr(s, "step_series"):
+        if _native(s, "step_series"):
             s.step_series(f, outs, self.tau, uvs, loss if uvs is not None else None, self.diss_weight or 0.0)
             return
         for k, out in enumerate(outs):
@@ -227,7 +240,7 @@ class Rollout:
             # the seed of the state after each step: none, or formed in the
             # step from its velocity field, or (w without such a field, or in
             # double precision) by a pass of its own
-            if hasattr(s, "adjoint_series") and pend_seed is None and (
+            if _native(s, "adjoint_series") and pend_seed is None and (
                     not w or (fused and all(u is not None for u in uvs[1:]) and (start == 0 or uvs[0] is not None))):
                 lam, other = s.adjoint_series(states[::-1], lam, other, self.tau,
                                               [pend_uv] + uvs[:0:-1] if w else None, w or 0.0, force_grad)
