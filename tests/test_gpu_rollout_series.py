@@ -1,5 +1,6 @@
 """The native sequences of a rollout (include/eselbm_rollout.h): argument errors
-of any of their calls come before the first is made."""
+of any of their calls come before the first is made, and a rollout through
+them equals one through single calls."""
 import ctypes
 
 import pytest
@@ -80,3 +81,44 @@ def test_adjoint_series_checks_every_call_first(es, bad):
     torch.cuda.synchronize()
     assert status == 1
     assert bool((lam == 1.0).all()) and bool((other == 7.0).all())
+
+
+class OneCallAtATime:
+    """A solver without the native sequences: the rollout's Python loops."""
+
+    def __init__(self, s):
+        self._s = s
+
+    def __getattr__(self, name):
+        if name in ("step_series", "adjoint_series"):
+            raise AttributeError(name)
+        return getattr(self._s, name)
+
+
+@pytest.mark.parametrize("nsteps,ckpt,keep", [(7, 3, 1), (6, 3, 2), (5, 1, 1), (4, 9, 1), (9, 2, None)])
+@pytest.mark.parametrize("D,dtype,force,diss", [
+    (2, "f32", False, None), (2, "f32", False, 1e-3), (2, "f64", False, 1e-3), (2, "f32s", False, 1e-3),
+    (3, "f32", True, 1e-3), (3, "f32", True, None), (3, "f64", False, None)])
+def test_native_sequences_equal_single_calls(es, D, dtype, force, diss, nsteps, ckpt, keep):
+    """State, loss and gradients to the bit: the same launches in the same order."""
+    from paper_2203_12946_amd.adjoint import Rollout
+    shape = (12, 70) if D == 2 else (4, 6, 66)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    s = es.Solver("D2Q9" if D == 2 else "D3Q27", shape, dtype=dtype)
+    rho = 1 + 1e-2 * torch.randn(shape, generator=g, device="cuda", dtype=torch.float64)
+    u = 0.02 * torch.randn((D,) + shape, generator=g, device="cuda", dtype=torch.float64)
+    f0 = s.init_equilibrium(rho, u)
+    lam = torch.randn(f0.shape, generator=g, device="cuda", dtype=torch.float64).to(s.compute_dtype)
+    F = 1e-5 * torch.randn((D,) + shape, generator=g, device="cuda") if force else None
+    if force:
+        s.set_force(F)
+    out = []
+    for solver in (s, OneCallAtATime(s)):
+        ro = Rollout(solver, 0.02, nsteps, ckpt, diss_weight=diss, keep_segments=keep)
+        loss = None if diss is None else torch.zeros(1, dtype=torch.float64, device="cuda")
+        fg = torch.zeros_like(F) if force else None
+        fN = ro.forward(f0, loss)
+        grad = ro.backward(lam, diss_grad=0.7 if diss else 0.0, force_grad=fg)
+        again = ro.backward(lam, diss_grad=0.7 if diss else 0.0)  # with every segment recomputed
+        out.append([t.clone() for t in (fN, grad, again, loss, fg) if t is not None])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
