@@ -531,9 +531,10 @@ struct SeriesCfgF16 {
 
 // Beyond X, up to X below, the same sums are taken again to order K in the
 // type of the exact path (alpha_extended), from one pass instead of the two
-// of the exact rationals.  The remainder of R sets the bound; it moves alpha by
-//   FP64:            X = 0.05, K = 14: under 5e-16, and the update by 3e-17 of g;
-//   4- and 2-byte:   X = 0.1,  K = 10: under 2e-8, and the update by 2e-9 of g.
+// of the exact rationals.  The remainder of R sets the bound; with every power
+// moment at its largest against T_2 it moves alpha by
+//   FP64:            X = 0.05, K = 14: under 1.1e-15, and the update by 6e-17 of g;
+//   4- and 2-byte:   X = 0.1,  K = 10: under 2.5e-8, and the update by 2.5e-9 of g.
 template <typename T>
 struct ExtendedCfg;
 template <>
@@ -563,8 +564,8 @@ constexpr double kR[12] = {1.25, -5.0 / 8.0, 3.0 / 8.0, -0.25, 45.0 / 256.0, -65
 //   float,  X = 0.02,  K = 6: the remainder moves alpha by under 1.2e-8
 //           (|T_7| <= X^5 T_2, entering dH as (a^7/42 - a/6) T_7);
 //   double, X = 0.005, K = 8: under 6e-16 (X^7 T_2 times a^9/72 - a/8).
-// Beyond X, the extended moments:
-//   float,  X = 0.18, K = 14: 4e-8;   double, X = 0.08, K = 18: 4e-16.
+// Beyond X, the extended moments (all omitted terms, dF/da down to 0.9 T_2):
+//   float,  X = 0.18, K = 14: 6e-8;   double, X = 0.08, K = 18: 6e-16.
 template <typename T>
 struct MirrorSeriesCfg;
 template <>
