@@ -119,14 +119,26 @@ constexpr long long kMaxFlatPlane = 1LL << 28;
 
 // Plain stores of a step's output (true), or non-temporal ones, which stream
 // past the caches.  Streaming is the faster way out of a grid whose two
-// lattices exceed the 256 MB last-level cache, and out of a small one, whose
-// dirty lines the L2s would write back at the end of the launch.  Plain stores
-// are faster
+// lattices exceed the 256 MB last-level cache, and out of one of some tens of
+// MB, whose dirty lines the L2s would write back at the end of the launch.
+// Plain stores are faster (per step, streaming / plain; lattices are pairs)
+//  - out of the smallest grids, whose stores the end of the launch would wait
+//    for: D2Q9 F32 64^2 3.31 / 3.06 us, 256^2 (4.7 MB) 4.36 / 4.12, FP64 192^2
+//    4.89 / 4.65, F16-shifted 384^2 4.69 / 4.47; D3Q27 F32 24^3 8.43 / 8.20,
+//    F16-shifted 32^3 7.34 / 7.07; beyond the line F16-shifted 36^3 (5.04 MB)
+//    10.2 / 10.8, F32 320^2 4.83 / 5.02, 512^2 6.25 / 7.81, FP64 256^2 6.33 / 6.55;
 //  - where the two lattices fit the last-level cache, from which the next step
-//    then reads (per step, streaming / plain: D2Q9 1024^2 FP64 34.7 / 26.1 us,
-//    F32 16.6 / 15.1, 1000^2 F32 15.7 / 14.0, 2048^2 F16-shifted 34.0 / 30.6;
-//    D3Q27 128^3 F16-shifted 53.1 / 47.1; at their other side 512^2 F32 6.0 /
-//    7.4, 64^3 F32 19.8 / 21.5, 1500^2 FP64 60 / 64, 256^3 F32 629 / 657);
+//    then reads, and the step waits for memory.  The line lies where the
+//    slowest of a type's steps has reached it:
+//    D2Q9   4 bytes: 50 MB F32 12.0 / 11.0 us but F32-shifted 13.4 / 14.0,
+//                    58 MB F32 14.1 / 12.8, 231 MB 41.9 / 37.8
+//           8 bytes: 59 MB 15.8 / 16.2, 71 MB 18.2 / 16.6, 236 MB 46.6 / 41.6
+//           2 bytes: 71 MB 17.7 / 18.9, 85 MB 20.9 / 20.5, 116 MB 25.8 / 26.7,
+//                    151 MB 35.9 / 33.6, 236 MB 48.5 / 47.8
+//    D3Q27  4 bytes: 57 MB F32 14.1 / 13.3 us but F32-shifted 13.8 / 15.1, 81 MB
+//                    20.7 / 17.2 and 20.8 / 19.4, 243 MB 48.4 / 44.0
+//           8 bytes: 113 MB 33.5 / 35.1, 161 MB 46.7 / 48.1, 221 MB 60.6 / 60.3
+//           2 bytes: 122 MB 38.4 / 39.5, 152 MB 40.1 / 38.6, 227 MB 51.0 / 46.5;
 //  - where the populations' fields do not start on cache lines (N elements no
 //    multiple of 128 bytes): a wave's row then ends in the middle of a line,
 //    which streams out in two partial writes and merges in the L2 (255x253x251
@@ -135,8 +147,11 @@ constexpr long long kMaxFlatPlane = 1LL << 28;
 inline bool cached_stores(const Grid &g, int elem)
 {
     const long long bytes = 2LL * g.Q * g.N * elem;
-    if (bytes < (g.D == 2 ? 55000000LL : 110000000LL)) return false;
-    return g.N * elem % 128 != 0 || bytes <= (256LL << 20);
+    if (bytes < 5000000LL) return true;
+    const long long line = g.D == 2 ? (elem == 2 ? 80 : elem == 4 ? 55 : 65) : (elem == 2 ? 140 : elem == 4 ? 70 : 210);
+    const bool odd = g.N * elem % 128 != 0;
+    if (bytes < (odd ? (g.D == 2 ? 55 : 110) : line) * 1000000LL) return false;
+    return odd || bytes <= (256LL << 20);
 }
 
 // Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx.
