@@ -25,11 +25,17 @@ namespace eselbm {
 //               568, 250x120x130 411 / 341; 16^3 6.8 / 7.2;
 //   D2Q9:       1500^2 66 / 63 (FP64), 33.5 / 30.9 (F32); 256^2 5.6 / 5.7,
 //               3.9 / 4.2; 1024^2 34.5 / 36.6, 16.7 / 16.6.
-//   cavities, D3Q27 F32: 192^3 308 / 288, 64^3 26.7 / 24.3, 128^3 101 / 110.
+//   cavities, D3Q27 F32: 192^3 308 / 288, 64^3 26.7 / 24.3, 128^3 101 / 110;
+//   rows of 192 cells, D3Q27: 192^3 F32 286 / 278, F32-shifted 291 / 283,
+//               F16-shifted 158 / 159, ES-BGK F32 445 / 404, cavity F32-shifted
+//               324 / 306; 192x48x48 F32 23.9 / 23.8; in place F32 306 / 307,
+//               F32-shifted 310 / 313;
+//   cavities with rows of 64: 64x200x100 F32 62.7 / 61.3, 64^3 F16-shifted
+//               17.9 / 17.0, F32-shifted 19.8 / 19.6, 64x40x40 F32 13.0 / 13.0.
 // So planes where rows are ragged and the grid is beyond the smallest (whose
-// step is latency), in D3Q27 also for rows of three waves (192 cells; not the
-// periodic F16-shifted step, 156 / 158) and the walled step's rows of one, and
-// for the FP64 D3Q27 step below 256 cells a row.
+// step is latency), in D3Q27 also for rows of three waves (192 cells; not in
+// place, and not the periodic F16-shifted step) and the walled step's rows of
+// one, and for the FP64 D3Q27 step below 256 cells a row.
 static bool use_flat(int dtype, const StepArgs &a)
 {
     const Grid &g = a.g;
@@ -37,7 +43,7 @@ static bool use_flat(int dtype, const StepArgs &a)
     const bool ragged = g.nx % 64 != 0 || (g.nx > 256 && g.nx % 256 != 0);
     if (g.D == 2) return ragged && g.N >= 1 << 18;
     if (dtype == 0) return (ragged || g.nx < 256) && g.N >= 1 << 15;
-    const bool three = g.nx == 192 && (dtype != 2 || a.walls || a.cpr != 0.0);
+    const bool three = g.nx == 192 && a.aa == 0 && (dtype != 2 || a.walls || a.cpr != 0.0);
     return (ragged || three || (a.walls && g.nx == 64)) && g.N >= 1 << 16;
 }
 
