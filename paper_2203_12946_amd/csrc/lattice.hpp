@@ -1094,12 +1094,27 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
     asm volatile("" : "+v"(xa), "+v"(alpha));
     if (!(xa < T(SC::X))) {
         info.exact = 1;
-        // alpha and its positivity guard (App. D) in A
-        A xm, al;
         constexpr bool mirror = is_mirror_mode(MODE), full = MODE == MODE_ELBM;
         using XC = typename std::conditional<mirror, MirrorExtendedCfg<T>, ExtendedCfg<T>>::type;
-        // one of the two forms per wave: the exact one where any cell needs it
-        if (__ballot(!(xa < T(XC::X))) == 0ull) {
+        A xm, al;
+        // alpha and its positivity guard (App. D) in A
+        auto guard = [&]() {
+            if (xm < A(0)) {
+                const A amax = A(-1) * rcp_(A(beta64) * xm);
+                if (al > amax) {
+                    al = A(0.5) * (A(1) + amax);
+                    info.guarded = 1;
+                }
+            }
+            alpha = T(al);
+        };
+        // Each cell takes the form of its own |x|, whatever cells share its
+        // wave (a translated flow keeps its bits).  A wave that needs one form
+        // skips the other, which is nearly every wave of a resolved flow
+        // (128^3 vortex, 64% of the cells here: FP64 237 us a step, as with one
+        // form per wave); grid-scale noise pays for both (128^3 F32 188 -> 234
+        // us, FP64 264 -> 325; by the rationals alone 196 and 476).
+        if (xa < T(XC::X)) {
             A Te[XC::K + 1], Ne[XC::K + 1];
             extended_moments<D, T, A, SH, XC::K, MODE == MODE_HIGHER ? XC::K : 3>(p, d, Te, Ne, xm);
             if constexpr (MODE == MODE_HIGHER) {
@@ -1108,18 +1123,12 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
                 al = lower_series<A, XC::K>(Te, Ne);
                 if constexpr (mirror) al = mirror_series<A, full, XC::K>(Te, al, xm, info);
             }
+            guard();
         } else {
             al = alpha_exact<D, T, A, mirror ? MODE_LOWER : MODE, SH>(p, d, A(beta64), xm);
             if constexpr (mirror) al = mirror_alpha<D, T, A, SH, full>(p, d, al, xm, info);
+            guard();
         }
-        if (xm < A(0)) {
-            const A amax = A(-1) * rcp_(A(beta64) * xm);
-            if (al > amax) {
-                al = A(0.5) * (A(1) + amax);
-                info.guarded = 1;
-            }
-        }
-        alpha = T(al);
     }
     return alpha;
 }
