@@ -311,9 +311,11 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         if (aa) dst = src;
         StepArgs sa;
         sa.fin = src;
-        sa.fout = dst;
-        sa.fout2 = pair && last ? f_out : nullptr;
-        sa.g = h->g;
+        sa.fout = pair && last ? f_out : dst;
+        sa.nx = h->g.nx;
+        sa.ny = h->g.ny;
+        sa.nz = h->g.nz;
+        sa.N = h->g.N;
         sa.beta = 1.0 / (2.0 * tau + 1.0);
         sa.force = h->force;
         sa.walls = h->walls;
@@ -338,7 +340,7 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
             if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
             else if (cap == hipStreamCaptureStatusNone) h->h_clear = 1;
         }
-        hipError_t e = launch_step(h->dtype, h->mode, diag, sa, s);
+        hipError_t e = launch_step(h->dtype, h->g.D, h->mode, diag, sa, s);
         if (e != hipSuccess) return hip_fail(e, "eselbm_step: launch");
         if (!aa) {
             void *t = src;

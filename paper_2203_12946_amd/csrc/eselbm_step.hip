@@ -36,33 +36,32 @@ namespace eselbm {
 // step is latency), in D3Q27 also for rows of three waves (192 cells; not in
 // place, and not the periodic F16-shifted step) and the walled step's rows of
 // one, and for the FP64 D3Q27 step below 256 cells a row.
-static bool use_flat(int dtype, const StepArgs &a)
+static bool use_flat(int dtype, int D, const StepArgs &a)
 {
-    const Grid &g = a.g;
-    if ((long long)g.nx * g.ny > kMaxFlatPlane) return false;
-    const bool ragged = g.nx % 64 != 0 || (g.nx > 256 && g.nx % 256 != 0);
-    if (g.D == 2) return ragged && g.N >= 1 << 18;
-    if (dtype == 0) return (ragged || g.nx < 256) && g.N >= 1 << 15;
-    const bool three = g.nx == 192 && a.aa == 0 && (dtype != 2 || a.walls || a.cpr != 0.0);
-    return (ragged || three || (a.walls && g.nx == 64)) && g.N >= 1 << 16;
+    if ((long long)a.nx * a.ny > kMaxFlatPlane) return false;
+    const bool ragged = a.nx % 64 != 0 || (a.nx > 256 && a.nx % 256 != 0);
+    if (D == 2) return ragged && a.N >= 1 << 18;
+    if (dtype == 0) return (ragged || a.nx < 256) && a.N >= 1 << 15;
+    const bool three = a.nx == 192 && a.aa == 0 && (dtype != 2 || a.walls || a.cpr != 0.0);
+    return (ragged || three || (a.walls && a.nx == 64)) && a.N >= 1 << 16;
 }
 
-hipError_t launch_step(int dtype, int mode, bool diag, const StepArgs &a, hipStream_t s)
+hipError_t launch_step(int dtype, int D, int mode, bool diag, const StepArgs &a, hipStream_t s)
 {
-    if (use_flat(dtype, a)) {
+    if (use_flat(dtype, D, a)) {
         switch (dtype) {
-        case 0: return launch_step_flat_f64(a.g.D, mode, diag, a, s);
-        case 1: return launch_step_flat_f32(a.g.D, mode, diag, a, s);
-        case 2: return launch_step_flat_f16s(a.g.D, mode, diag, a, s);
-        case 3: return launch_step_flat_f32s(a.g.D, mode, diag, a, s);
+        case 0: return launch_step_flat_f64(D, mode, diag, a, s);
+        case 1: return launch_step_flat_f32(D, mode, diag, a, s);
+        case 2: return launch_step_flat_f16s(D, mode, diag, a, s);
+        case 3: return launch_step_flat_f32s(D, mode, diag, a, s);
         }
         return hipErrorInvalidValue;
     }
     switch (dtype) {
-    case 0: return launch_step_f64(a.g.D, mode, diag, a, s);
-    case 1: return launch_step_f32(a.g.D, mode, diag, a, s);
-    case 2: return launch_step_f16s(a.g.D, mode, diag, a, s);
-    case 3: return launch_step_f32s(a.g.D, mode, diag, a, s);
+    case 0: return launch_step_f64(D, mode, diag, a, s);
+    case 1: return launch_step_f32(D, mode, diag, a, s);
+    case 2: return launch_step_f16s(D, mode, diag, a, s);
+    case 3: return launch_step_f32s(D, mode, diag, a, s);
     }
     return hipErrorInvalidValue;
 }

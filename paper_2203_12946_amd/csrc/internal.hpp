@@ -28,28 +28,34 @@ struct Grid {
 // What every step reads comes first, in one 64-byte line: a line more is a
 // read more that a small grid's step, a few microseconds long, waits for (per
 // step against one reference build: D2Q9 64^2 FP64 1.028 -> 0.993 of its time,
-// 128^2 F32 1.056 -> 1.028, D3Q27 22^3 FP64 1.026 -> 1.023).
+// 128^2 F32 1.056 -> 1.028, D3Q27 22^3 FP64 1.026 -> 1.023).  112 bytes in all,
+// and the kernels read no launch dimensions, of which the compiler would append
+// 256 bytes: the host's time to enqueue a launch, which bounds the smallest
+// grids, steps up between 112 and 120 bytes (a kernel of 64 blocks, 100 launches
+// after a synchronisation: 3.1 us a launch up to 112 bytes, 3.7-4.4 from 120,
+// 4.1-4.7 with 144 and the dimensions).
 struct StepArgs {
     const void *fin;
-    void *fout;
-    Grid g;
+    void *fout;          // in place: fin, or for the local half a second copy of its output
+    int nx, ny, nz;
+    unsigned walls : 8;  // bit a: axis a bounded by diffuse walls, else periodic
+    unsigned cached : 8; // plain stores, else non-temporal ones (cached_stores)
+    unsigned aa : 16;    // 0: two lattices (fin -> fout); in place: 1 the pull half, 2 the local half
+    long long N;         // cells
     double beta;
-    int cached;          // plain stores, else non-temporal ones (cached_stores)
-    int walls;           // bit a: axis a bounded by diffuse walls, else periodic
     double inv_nx;       // 1 / nx, for the plane-mapped launches
     const float *force;  // [D][N] or null
     const double *wall_eq;   // [2 D][Q]: feq_i(1, u_wall) - w_i of wall 2 a + side
     double cpr;          // ES-BGK stress factor c_Pr; 0: the equilibrium itself
-    void *fout2;         // or null; in place, the local half's output once more
     void *alpha_out;     // [N] compute type or null
     void *nut_out;       // [N] compute type or null: nu_T of Eq. nuT
     float *uv_out;       // [D + 1][N] or null: u (with the half-force shift) and rho of the output state
     DevStats *stats;     // kStatSlots slots or null
-    int aa;              // 0: two lattices (fin -> fout); in place: 1 the pull half, 2 the local half
 };
+static_assert(sizeof(StepArgs) == 112, "at most 112 bytes (above)");
 
 // Launchers (return the hipError_t of the launch).
-hipError_t launch_step(int dtype, int mode, bool diag, const StepArgs &a, hipStream_t s);
+hipError_t launch_step(int dtype, int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
 // the step for one storage type (step_<type>.hip)
 hipError_t launch_step_f64(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
 hipError_t launch_step_f32(int D, int mode, bool diag, const StepArgs &a, hipStream_t s);
@@ -157,8 +163,10 @@ inline bool cached_stores(const Grid &g, int elem)
     return odd || bytes <= (256LL << 20);
 }
 
-// Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx.
-inline int block_x(int nx)
+// Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx;
+// of a plane-mapped launch.
+constexpr unsigned kFlatBlock = 256;
+__host__ __device__ inline int block_x(int nx)
 {
     int w = (nx + 63) / 64;
     if (w > 4) w = 4;

@@ -61,7 +61,7 @@ struct LaneStats {
 // take the place of a six-step exchange each (128^3, the step with its
 // statistics: F32 94.6 -> 91.4 us, F16-shifted 83 -> 71 us).
 template <bool ITER>
-__device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot)
+__device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot, int nw)
 {
     constexpr int NU = 8;  // counters
     __shared__ double red_d[4][6];
@@ -83,7 +83,6 @@ __device__ inline void block_reduce_stats(LaneStats &s, DevStats *slot)
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int nw = (blockDim.x + 63) >> 6;
         DevStats *st = slot;
         double t[6] = {0, 0, 0, 0, 0, 0};
         unsigned long long u[NU] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -293,9 +292,9 @@ __device__ inline void pull_walls(const StepArgs &a, int x, int y, int z, typena
     using T = typename Storage<S>::T;
     constexpr int Q = Lat<D>::Q;
     constexpr bool SH = Storage<S>::kShifted;
-    const int n[3] = {a.g.nx, a.g.ny, a.g.nz};
+    const int n[3] = {a.nx, a.ny, a.nz};
     const int xc[3] = {x, y, z};
-    const long long N = a.g.N, cell = ((long long)z * n[1] + y) * n[0] + x;
+    const long long N = a.N, cell = ((long long)z * n[1] + y) * n[0] + x;
     const S *__restrict__ fin = (const S *)a.fin;
     // per axis and velocity component c (at c + 1): the source coordinate,
     // wrapped, and the wall beyond which it lies (2 k + side, -1: none);
@@ -373,7 +372,7 @@ __device__ inline void fix_x_wall(const StepArgs &a, long long cell, typename St
     constexpr int Q = Lat<D>::Q;
     constexpr bool SH = Storage<S>::kShifted;
     constexpr int CS = SIDE == 0 ? 1 : -1;
-    const long long N = a.g.N;
+    const long long N = a.N;
     const S *__restrict__ fin = (const S *)a.fin;
     using E = typename std::conditional<StepPolicy<S>::mom_f64, double, T>::type;
     E out_dev = E(0), in_dev = E(0), in_w = E(0);
@@ -417,11 +416,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
     using T = typename Storage<S>::T;
     using Pol = StepPolicy<S>;
     constexpr int Q = Lat<D>::Q;
-    const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
-    const long long N = a.g.N;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const long long N = a.N;
     const int z = (int)blockIdx.z;
     // the lane's offset in its row, or (FLAT) in its plane
-    const unsigned lx = blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned bx = FLAT ? kFlatBlock : (unsigned)block_x(nx);
+    const unsigned lx = blockIdx.x * bx + threadIdx.x;
     // in place the two pointers are the same buffer: no restrict there
     using InP = typename std::conditional<AA == kTwoLattice, const S *__restrict__, const S *>::type;
     using OutP = typename std::conditional<AA == kTwoLattice, S *__restrict__, S *>::type;
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
     // (an input of an empty asm), and not on first use, where a small grid's
     // step waits for them (D2Q9 F32, per step of a graph: 64^2 2.98 -> 2.95 us,
     // 128^2 3.11 -> 3.07)
-    const int cached = a.cached;
+    const unsigned cached = a.cached;
     asm volatile("" :: "s"(fout), "s"(cached));
     // the LDS columns of the stored values a double-precision step parks
     __shared__ T stash[stash_pops<D, S, MODE, WALL, QE, AA>() > 0 ? stash_pops<D, S, MODE, WALL, QE, AA>() * kStashStride : 1];
@@ -616,11 +616,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
         };
         // (the empty asm keeps the compiler from joining the branches' stores
         // and dropping the hint)
+        OutP own = AA == kAALocal ? (OutP)a.fin : fout;
         if (cached) {
-            put(fout, [](S *q, S v) { *q = v; });
+            put(own, [](S *q, S v) { *q = v; });
             asm volatile("; end of cached stores");
         } else {
-            put(fout, [](S *q, S v) { Storage<S>::store_nt(q, v); });
+            put(own, [](S *q, S v) { Storage<S>::store_nt(q, v); });
         }
         if constexpr (AA == kAALocal) {
             // the last of an even count of steps on two lattices leaves its
@@ -628,12 +629,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             // reads this copy (two steps a call, streaming / plain where
             // cached_stores chooses plain: D2Q9 1024^2 FP64 67.3 / 63.0 us, F32
             // 35.8 / 35.3)
-            if (a.fout2) {
+            if (fout != own) {
                 if (cached) {
-                    put((OutP)a.fout2, [](S *q, S v) { *q = v; });
+                    put(fout, [](S *q, S v) { *q = v; });
                     asm volatile("; end of cached stores");
                 } else {
-                    put((OutP)a.fout2, [](S *q, S v) { Storage<S>::store_nt(q, v); });
+                    put(fout, [](S *q, S v) { Storage<S>::store_nt(q, v); });
                 }
             }
         }
@@ -684,7 +685,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
             }
         }
     }
-    if (DIAG && a.stats) block_reduce_stats<QE || is_mirror_mode(MODE)>(ls, a.stats + ((FLAT ? blockIdx.x : blockIdx.y) + blockIdx.z) % kStatSlots);
+    if (DIAG && a.stats) block_reduce_stats<QE || is_mirror_mode(MODE)>(ls, a.stats + ((FLAT ? blockIdx.x : blockIdx.y) + blockIdx.z) % kStatSlots, (int)(bx >> 6));
 }
 
 // Occupancy cap of the D3Q27 alpha = 2 steps in the 4- and 2-byte formats.
@@ -713,10 +714,10 @@ static hipError_t launch_step_t(bool diag, const StepArgs &a, hipStream_t s)
 {
     // (x-block, y, z), or (plane block, 1, z); the API limits ny and nz to the
     // grid's 65535
-    const int bx = FLAT ? 256 : block_x(a.g.nx);
-    if (a.g.ny > 65535 || a.g.nz > 65535) return hipErrorInvalidConfiguration;
-    const long long line = FLAT ? (long long)a.g.nx * a.g.ny : a.g.nx;
-    const dim3 grid((unsigned)((line + bx - 1) / bx), FLAT ? 1u : (unsigned)a.g.ny, (unsigned)a.g.nz), block(bx);
+    const int bx = FLAT ? (int)kFlatBlock : block_x(a.nx);
+    if (a.ny > 65535 || a.nz > 65535) return hipErrorInvalidConfiguration;
+    const long long line = FLAT ? (long long)a.nx * a.ny : a.nx;
+    const dim3 grid((unsigned)((line + bx - 1) / bx), FLAT ? 1u : (unsigned)a.ny, (unsigned)a.nz), block(bx);
     const bool force = a.force != nullptr;
     if (a.aa != kTwoLattice) {
         // in place: periodic, the closed-form and alpha = 2 modes
