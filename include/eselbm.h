@@ -131,12 +131,14 @@ typedef enum {
  *             pulled populations (in the LBGK mode, which needs no
  *             logarithm, every finite cell is collided and counted).
  *   n_alpha_lt2  cells with alpha < 2.
- *   n_exact   cells whose path length was evaluated with the exact rational
- *             sums (cells with all |x_i| below 0.02 in single precision and
- *             0.005 in double are evaluated through truncated power series
- *             of the same sums, accurate to the rounding of the type).
- *             In the ELBM and ITERATE1 modes: cells beyond that bound, whose
- *             condition takes a longer series or the logarithms themselves.
+ *   n_exact   cells beyond the common series of the path length's sums (all
+ *             |x_i| below 0.02 in the 4-byte types, 0.01 in F16-shifted and
+ *             0.005 in double: truncated power series, accurate to the
+ *             rounding of the type).  Their sums take a longer series (all
+ *             |x_i| below 0.1, in double 0.05) or the exact rationals.
+ *             In the ELBM and ITERATE1 modes: cells beyond 0.02 (0.005 in
+ *             double), whose condition takes a longer series or the
+ *             logarithms themselves.
  *   n_newton  ELBM and ITERATE1 modes: Newton iterations summed over cells;
  *             with ES-BGK on (eselbm_set_prandtl), the quasi-equilibrium's
  *             Newton iterations.

@@ -15,6 +15,9 @@
 // alpha = 2 is constant; where the positivity guard fires,
 // alpha = (1 - 1/(beta x_min)) / 2 depends only on the smallest x_i (lowest
 // index on ties).
+// Cells beyond the common series are differentiated through the exact rational
+// sums, also where the step takes its extended series of them, which differs by
+// rounding (ExtendedCfg).
 #include "internal.hpp"
 #include "lattice.hpp"
 
@@ -274,7 +277,7 @@ __device__ inline void root_bar(T s, T A, T B, T sbar, T &Ab, T &Bb, T &Cb)
 // issue exceeds its memory time), and a third wave per SIMD hides more of its
 // memory latency.  In single precision the Q values of x and of lambda, the
 // equilibrium tables and the adjoints of the sums fit 168 VGPRs in the
-// alpha_Higher and BGK kernels, the forced alpha_Higher kernel with four
+// alpha_Higher and BGK kernels, the forced alpha_Higher kernel with five
 // registers spilled once per lane (128^3 forced: 182 us per launch against
 // 190 us at two waves, on one box).  Parking x in LDS instead (27 KiB per
 // block, 147 VGPRs, no scratch) measured 190 us.  The D3Q27 alpha_Lower

@@ -1,14 +1,6 @@
-// Forward kernels: the fused pull-stream + entropic collision step, the
-// equilibrium initialiser, and the double-precision diagnostics (moments,
-// H function, fused step statistics).
-//
-// Mapping: one lattice cell per lane.  A block is 64..256 lanes along one
-// x-row; the grid is (x-blocks, y, z).  Each lane pulls its Q
-// populations from the neighbouring rows (Eq. advection): every population
-// load of a wave is 64 consecutive elements of one row, shifted by at most
-// one element, so loads stay coalesced; every store is aligned.  Each
-// element of f_in is read exactly once over the whole grid, so there is no
-// reuse for LDS or an XCD-aware block order to capture.
+// The step's dispatch (by storage type and lane mapping; the kernel is in
+// step_kernel.hpp), the equilibrium initialiser, and the double-precision
+// diagnostics (moments, H function, the statistics' reset).
 #include "step_kernel.hpp"
 
 namespace eselbm {

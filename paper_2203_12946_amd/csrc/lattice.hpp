@@ -456,7 +456,7 @@ __device__ inline void equilibrium_shifted(T drho, const T (&u)[3], T (&feqt)[La
 }
 
 struct CellInfo {
-    int gated, guarded, exact;  // exact: the exact rational path ran
+    int gated, guarded, exact;  // exact: beyond the common series
     int iters, fallback;        // mirror modes: Newton iterations; alpha_Lower kept
 };
 
@@ -483,9 +483,11 @@ __device__ inline T conj_root(T a, T b, T c)
 //   a  = beta^2 (N3/6 - h beta N4/12 + (h beta)^2 N5/20 - (h beta)^3 N6/5),
 //        N_k = <g, x^k>_-
 //
-// Two evaluations of the rational sums:
+// Three evaluations of the rational sums, by the cell's own max|x|:
 //  * exact: the rational functions per population (c1 and c share one
 //    reciprocal of (2 + x)(60 + 90x + 36x^2 + 3x^3));
+//  * extended series, |x| below the bound of ExtendedCfg: as the next, to a
+//    higher order and in the type of the exact sums;
 //  * series, used in a cell whose populations all have |x| < X (SeriesCfg):
 //    the sums through the power moments T_k = <g, x^k>, N_k = <g, x^k>_-,
 //    P_k = T_k - N_k (k <= K) and the Taylor series of the three rational
@@ -494,8 +496,7 @@ __device__ inline T conj_root(T a, T b, T c)
 //      x^2 N3/P3   = x^2 - x^3/2 + x^4/3 - x^5/4 + x^6/5 - x^7/6 + 57x^8/400 ...
 //      R(y)        = 5/4 - 5y/8 + 3y^2/8 - y^3/4 + 45y^4/256 - 65y^5/512 ...
 //    truncated where the remainder is below the rounding of the arithmetic
-//    type; it needs no reciprocal beyond 1/g.  Cells beyond the bound take
-//    the exact path.
+//    type; it needs no reciprocal beyond 1/g.
 // ---------------------------------------------------------------------------
 constexpr double kGate = 1e-3;
 
@@ -530,8 +531,8 @@ struct SeriesCfgF16 {
 };
 
 // Beyond X, up to X below, the same sums are taken again to order K in the
-// type of the exact path (alpha_extended), from one pass instead of the two
-// of the exact rationals.  The remainder of R sets the bound; with every power
+// type of the exact path, from one pass instead of the two
+// of the exact rationals (extended_moments).  The remainder of R sets the bound; with every power
 // moment at its largest against T_2 it moves alpha by
 //   FP64:            X = 0.05, K = 14: under 1.1e-15, and the update by 6e-17 of g;
 //   4- and 2-byte:   X = 0.1,  K = 10: under 2.5e-8, and the update by 2.5e-9 of g.
@@ -910,7 +911,8 @@ __device__ __attribute__((always_inline)) inline A mirror_newton(DH dH, A aL, A 
 // The leading term of G, T_2 (a/2 - 1), carries no cancellation, unlike the
 // difference of two sums.  With this, the extended moments and the row-wise
 // passes of mirror_alpha the modes run at the plain step's registers and occupancy
-// (F32 D3Q27: 256 -> 121 VGPRs, two -> four waves per SIMD).  150x150x120,
+// (F32 D3Q27: 256 -> 121 VGPRs, two -> four waves per SIMD; the diagnostic and
+// forced variants spill two to six registers there).  150x150x120,
 // per step, in a developed near-inviscid vortex: ELBM 306 -> 164 us (F32),
 // 598 -> 301 us (FP64); one Newton step 264 -> 189 us (F32).
 template <typename T, bool FULL, int K>
@@ -1112,8 +1114,9 @@ __device__ __attribute__((always_inline)) inline T path_length(const P &p, const
         // wave (a translated flow keeps its bits).  A wave that needs one form
         // skips the other, which is nearly every wave of a resolved flow
         // (128^3 vortex, 64% of the cells here: FP64 237 us a step, as with one
-        // form per wave); grid-scale noise pays for both (128^3 F32 188 -> 234
-        // us, FP64 264 -> 325; by the rationals alone 196 and 476).
+        // form per wave); a cavity's rows below the lid (192^3 F32 317 -> 322 us,
+        // 101^3 FP64 172 -> 183) and grid-scale noise pay for both (128^3 F32
+        // 188 -> 234 us, FP64 264 -> 325; by the rationals alone 196 and 476).
         if (xa < T(XC::X)) {
             A Te[XC::K + 1], Ne[XC::K + 1];
             extended_moments<D, T, A, SH, XC::K, MODE == MODE_HIGHER ? XC::K : 3>(p, d, Te, Ne, xm);

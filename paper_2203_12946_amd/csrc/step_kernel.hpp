@@ -2,12 +2,15 @@
 // templates, instantiated once per storage type in step_<type>.hip.
 //
 // Mapping: one lattice cell per lane.  A block is 64..256 lanes along one
-// x-row; the grid is (x-blocks, y, z).  Each lane pulls its Q
-// populations from the neighbouring rows (Eq. advection): every population
-// load of a wave is 64 consecutive elements of one row, shifted by at most
-// one element, so loads stay coalesced; every store is aligned.  Each
-// element of f_in is read exactly once over the whole grid, so there is no
-// reuse for LDS or an XCD-aware block order to capture.
+// x-row and the grid (x-blocks, y, z), or 256 lanes through a whole plane and
+// the grid (plane blocks, 1, z) (FLAT; use_flat says where).  Each lane pulls
+// its Q populations from the neighbouring rows (Eq. advection): a population's
+// loads of a wave are consecutive elements of a row (of two or more where a
+// plane-mapped wave crosses row ends), shifted by at most one element, so loads
+// stay coalesced; the stores are consecutive and unshifted, and start on cache
+// lines where the fields do (cached_stores).  Each element of f_in is read
+// exactly once over the whole grid, so there is no reuse for LDS or an
+// XCD-aware block order to capture.
 #pragma once
 
 #include "internal.hpp"
