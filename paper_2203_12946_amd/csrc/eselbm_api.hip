@@ -326,7 +326,7 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         sa.stats = (last && h->stats_on) ? h->dev_stats : nullptr;
         sa.cpr = cpr;
         sa.inv_nx = 1.0 / (double)h->g.nx;
-        sa.cached = cached_stores(h->g, (int)elem_size(h->dtype));
+        sa.cached = cached_stores(h->g, (int)elem_size(h->dtype), in_place) | cached_copy(h->g, (int)elem_size(h->dtype)) << 1;
         sa.aa = aa ? (k % 2 == 0 ? 1 : 2) : 0;
         // the forced step writes the velocity field itself; the others do it
         // in their diagnostic variant

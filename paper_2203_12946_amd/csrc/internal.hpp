@@ -39,7 +39,7 @@ struct StepArgs {
     void *fout;          // in place: fin, or for the local half a second copy of its output
     int nx, ny, nz;
     unsigned walls : 8;  // bit a: axis a bounded by diffuse walls, else periodic
-    unsigned cached : 8; // plain stores, else non-temporal ones (cached_stores)
+    unsigned cached : 8; // bit 0: plain stores, else non-temporal ones (cached_stores); bit 1: of the second copy
     unsigned aa : 16;    // 0: two lattices (fin -> fout); in place: 1 the pull half, 2 the local half
     long long N;         // cells
     double beta;
@@ -149,19 +149,33 @@ constexpr long long kMaxFlatPlane = 1LL << 28;
 //    multiple of 128 bytes): a wave's row then ends in the middle of a line,
 //    which streams out in two partial writes and merges in the L2 (255x253x251
 //    F32 979 / 805 us, FP64 1732 / 1558, F16-shifted 558 / 439; 203x97x131 F32
-//    141 / 130; 101x99x97 F32 54 / 46).
+//    141 / 130; 101x99x97 F32 54 / 46); in D2Q9 4- and 2-byte types not between
+//    320 MB and 1 GB (F32 302 MB 74.8 / 67.7, 450 MB 85.9 / 90.7, 648 MB 129.5 /
+//    132.8, 1152 MB 238 / 226; F16-shifted 576 MB 130 / 134; FP64 604 MB 138 / 128).
 // In place the same holds, by the same lines (128^3 F16-shifted 54.8 / 52.3 us,
 // 96^3 F32 36.8 / 35.0, 1024^2 FP64 32.1 / 29.1, 101x99x97 F32 46.6 / 42.3,
-// 203x97x131 F32 125 / 121).
-inline bool cached_stores(const Grid &g, int elem)
+// 203x97x131 F32 125 / 121), but D2Q9 beyond the last-level cache streams
+// (2049x2047 F32 56.7 / 62.4; larger ones within 2% either way).
+inline long long lattices_bytes(const Grid &g, int elem) { return 2LL * g.Q * g.N * elem; }
+constexpr long long kLastLevelCache = 256LL << 20;
+inline bool cached_stores(const Grid &g, int elem, bool in_place)
 {
-    const long long bytes = 2LL * g.Q * g.N * elem;
+    const long long bytes = lattices_bytes(g, elem);
     if (bytes < 5000000LL) return true;
     const long long line = g.D == 2 ? (elem == 2 ? 80 : elem == 4 ? 55 : 65) : (elem == 2 ? 140 : elem == 4 ? 70 : 210);
     const bool odd = g.N * elem % 128 != 0;
     if (bytes < (odd ? (g.D == 2 ? 55 : 110) : line) * 1000000LL) return false;
-    return odd || bytes <= (256LL << 20);
+    if (bytes <= kLastLevelCache) return true;
+    return odd && !(g.D == 2 && (in_place || (elem < 8 && bytes > 320000000LL && bytes < 1000000000LL)));
 }
+
+// The second copy of an even count's last step: plain where the lattices fit the
+// last-level cache, from which the caller's next step then reads it.  Two steps a
+// call, its stores streaming / plain: D2Q9 1024^2 FP64 65.7 / 62.0 us, F32 36.8 /
+// 36.1, 512^2 FP64 22.5 / 21.1, D3Q27 64^3 FP64 75.8 / 67.0, 128^3 F16-shifted
+// 108.1 / 103.1; beyond it 203x97x131 F32 310 / 340, 2999x3001 F32 339 / 370, 241^3
+// FP64 3440 / 3572, 256^3 F32 1698 / 1730 (F16-shifted 241^3 1066 / 997).
+inline bool cached_copy(const Grid &g, int elem) { return lattices_bytes(g, elem) <= kLastLevelCache; }
 
 // Block shape along x: 64-lane waves, up to 4 per block, enough to cover nx;
 // of a plane-mapped launch.

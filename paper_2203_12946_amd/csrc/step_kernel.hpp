@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
         // (the empty asm keeps the compiler from joining the branches' stores
         // and dropping the hint)
         OutP own = AA == kAALocal ? (OutP)a.fin : fout;
-        if (cached) {
+        if (cached & 1) {
             put(own, [](S *q, S v) { *q = v; });
             asm volatile("; end of cached stores");
         } else {
@@ -628,12 +628,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves_
         }
         if constexpr (AA == kAALocal) {
             // the last of an even count of steps on two lattices leaves its
-            // state in both, by the same kind of stores: the caller's next step
-            // reads this copy (two steps a call, streaming / plain where
-            // cached_stores chooses plain: D2Q9 1024^2 FP64 67.3 / 63.0 us, F32
-            // 35.8 / 35.3)
+            // state in both (the kind of stores: cached_copy)
             if (fout != own) {
-                if (cached) {
+                if (cached & 2) {
                     put(fout, [](S *q, S v) { *q = v; });
                     asm volatile("; end of cached stores");
                 } else {
