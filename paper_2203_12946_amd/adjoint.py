@@ -78,6 +78,8 @@ class Rollout:
         self.ckpt_uv: dict[int, torch.Tensor] = {}
         self.tail: dict[int, tuple[torch.Tensor, torch.Tensor | None]] = {}
         self.uv_end: torch.Tensor | None = None
+        # whether _steps makes native calls (looked up at the start of a sweep)
+        self.native = False
 
     def _steps(self, f: torch.Tensor, outs: list, uvs: list | None = None, loss: torch.Tensor | None = None):
         """One step f -> outs[0] -> outs[1] ... each; with ``uvs`` the velocity
@@ -87,7 +89,7 @@ class Rollout:
         s = self.s
         if not outs:
             return
-        if _native(s, "step_series"):
+        if self.native:
             s.step_series(f, outs, self.tau, uvs, loss if uvs is not None else None, self.diss_weight or 0.0)
             return
         for k, out in enumerate(outs):
@@ -138,6 +140,7 @@ class Rollout:
         """State after nsteps; with a dissipation weight, adds the loss of
         every state f^1..f^n to ``loss_acc`` (a device float64 scalar)."""
         s = self.s
+        self.native = _native(s, "step_series")
         self.ckpts, self.ckpt_uv, self.tail, self.uv_end = {}, {}, {}, None
         self.kept = self._resolve_kept()
         cur = f0.clone()
@@ -182,6 +185,7 @@ class Rollout:
         """Adjoint of the initial state given dL/df^n (may be None = 0) and the
         gradient of the accumulated dissipation loss; accumulates dL/dF."""
         s = self.s
+        self.native, native = _native(s, "step_series"), _native(s, "adjoint_series")
         lam = s.empty_adjoint()
         if lam_final is None:
             lam.zero_()
@@ -240,7 +244,7 @@ class Rollout:
             # the seed of the state after each step: none, or formed in the
             # step from its velocity field, or (w without such a field, or in
             # double precision) by a pass of its own
-            if _native(s, "adjoint_series") and pend_seed is None and (
+            if native and pend_seed is None and (
                     not w or (fused and all(u is not None for u in uvs[1:]) and (start == 0 or uvs[0] is not None))):
                 lam, other = s.adjoint_series(states[::-1], lam, other, self.tau,
                                               [pend_uv] + uvs[:0:-1] if w else None, w or 0.0, force_grad)

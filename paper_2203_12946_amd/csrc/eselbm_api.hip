@@ -289,9 +289,9 @@ static eselbm_status step_check(eselbm_handle h, const void *f_in, const void *f
     return ESELBM_OK;
 }
 
-eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, double tau, void *stream)
+// eselbm_step after its checks
+static eselbm_status step_run(eselbm_handle h, void *f_in, void *f_out, int nsteps, double tau, void *stream)
 {
-    if (eselbm_status st = step_check(h, f_in, f_out, nsteps, tau)) return st;
     const double cpr = stress_factor(h, tau);
     const bool in_place = f_in == f_out;
     hipStream_t s = (hipStream_t)stream;
@@ -357,6 +357,12 @@ eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, 
         h->last_out = f_out;
     }
     return ESELBM_OK;
+}
+
+eselbm_status eselbm_step(eselbm_handle h, void *f_in, void *f_out, int nsteps, double tau, void *stream)
+{
+    if (eselbm_status st = step_check(h, f_in, f_out, nsteps, tau)) return st;
+    return step_run(h, f_in, f_out, nsteps, tau, stream);
 }
 
 eselbm_status eselbm_alpha_stats(eselbm_handle h, eselbm_stats *out, int with_H, void *stream)
@@ -446,14 +452,13 @@ static eselbm_status adjoint_diss_check(eselbm_handle h, const float *uv_next, d
     return ESELBM_OK;
 }
 
-// The adjoint step behind both entry points: the loss seed of the state
-// after the step, if any, comes as a compact seed (seed_next) or as that
-// state's velocity field (seed_uv), whose dissipation seed the kernel forms.
-static eselbm_status adjoint_step_impl(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
-                                       const float *seed_uv, double seed_w, void *lam_n, double tau, void *force_grad,
-                                       void *stream, const char *who)
+// The adjoint step behind both entry points, after its checks: the loss seed of
+// the state after the step, if any, comes as a compact seed (seed_next) or as
+// that state's velocity field (seed_uv), whose dissipation seed the kernel forms.
+static eselbm_status adjoint_run(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
+                                 const float *seed_uv, double seed_w, void *lam_n, double tau, void *force_grad,
+                                 void *stream, const char *who)
 {
-    if (eselbm_status st = adjoint_check(h, f_n, lam_next, seed_next, lam_n, tau, force_grad, who)) return st;
     AdjArgs a;
     a.fn = f_n;
     a.lam_next = lam_next;
@@ -473,16 +478,19 @@ static eselbm_status adjoint_step_impl(eselbm_handle h, const void *f_n, const v
 eselbm_status eselbm_adjoint_step(eselbm_handle h, const void *f_n, const void *lam_next, const void *seed_next,
                                   void *lam_n, double tau, void *force_grad, void *stream)
 {
-    return adjoint_step_impl(h, f_n, lam_next, seed_next, nullptr, 0.0, lam_n, tau, force_grad, stream,
-                             "eselbm_adjoint_step");
+    if (eselbm_status st = adjoint_check(h, f_n, lam_next, seed_next, lam_n, tau, force_grad, "eselbm_adjoint_step"))
+        return st;
+    return adjoint_run(h, f_n, lam_next, seed_next, nullptr, 0.0, lam_n, tau, force_grad, stream, "eselbm_adjoint_step");
 }
 
 eselbm_status eselbm_adjoint_step_diss(eselbm_handle h, const void *f_n, const void *lam_next, const float *uv_next,
                                        double weight, void *lam_n, double tau, void *force_grad, void *stream)
 {
     if (eselbm_status st = adjoint_diss_check(h, uv_next, weight, lam_n)) return st;
-    return adjoint_step_impl(h, f_n, lam_next, nullptr, uv_next, weight, lam_n, tau, force_grad, stream,
-                             "eselbm_adjoint_step_diss");
+    if (eselbm_status st = adjoint_check(h, f_n, lam_next, nullptr, lam_n, tau, force_grad, "eselbm_adjoint_step_diss"))
+        return st;
+    return adjoint_run(h, f_n, lam_next, nullptr, uv_next, weight, lam_n, tau, force_grad, stream,
+                       "eselbm_adjoint_step_diss");
 }
 
 eselbm_status eselbm_kinetic_loss(eselbm_handle h, const void *f, double *loss_dev, void *lam, double scale,
@@ -551,14 +559,20 @@ static eselbm_status loss_uv_check(eselbm_handle h, const float *uv, const void 
     return ESELBM_OK;
 }
 
-eselbm_status eselbm_dissipation_loss_uv(eselbm_handle h, const float *uv, double *loss_dev, void *lam, void *seed,
-                                         double weight, void *force_grad, void *stream)
+static eselbm_status loss_uv_run(eselbm_handle h, const float *uv, double *loss_dev, void *lam, void *seed, double weight,
+                                 void *force_grad, void *stream)
 {
-    if (eselbm_status st = loss_uv_check(h, uv, lam, seed, force_grad)) return st;
     hipError_t e = launch_dissipation_loss(h->loss_scratch, h->dtype, h->g, nullptr, uv, h->force, loss_dev, lam, seed,
                                            weight, (float *)force_grad, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "eselbm_dissipation_loss_uv: launch");
     return ESELBM_OK;
+}
+
+eselbm_status eselbm_dissipation_loss_uv(eselbm_handle h, const float *uv, double *loss_dev, void *lam, void *seed,
+                                         double weight, void *force_grad, void *stream)
+{
+    if (eselbm_status st = loss_uv_check(h, uv, lam, seed, force_grad)) return st;
+    return loss_uv_run(h, uv, loss_dev, lam, seed, weight, force_grad, stream);
 }
 
 eselbm_status eselbm_equilibrium_vjp(eselbm_handle h, const double *rho, const double *u, const void *lam,
@@ -578,7 +592,7 @@ eselbm_status eselbm_rollout_steps(eselbm_handle h, const void *f, void *const *
     if (!h || !f || !states) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: NULL argument");
     if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: n must be >= 1");
     if (loss_dev && !uvs) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: the loss needs velocity fields");
-    // every call's arguments before the first is made
+    // every call's arguments before the first is made, and not again with it
     void *src = const_cast<void *>(f);  // one step at a time: eselbm_step does not write its input
     for (int k = 0; k < n; ++k) {
         if (states[k] == src) return fail(ESELBM_E_ARG, "eselbm_rollout_steps: a step onto its own input");
@@ -591,9 +605,9 @@ eselbm_status eselbm_rollout_steps(eselbm_handle h, const void *f, void *const *
     src = const_cast<void *>(f);
     for (int k = 0; k < n && st == ESELBM_OK; ++k) {
         if (uvs) h->uv_field = uvs[k];
-        st = eselbm_step(h, src, states[k], 1, tau, stream);
+        st = step_run(h, src, states[k], 1, tau, stream);
         if (st == ESELBM_OK && loss_dev)
-            st = eselbm_dissipation_loss_uv(h, uvs[k], loss_dev, nullptr, nullptr, weight, nullptr, stream);
+            st = loss_uv_run(h, uvs[k], loss_dev, nullptr, nullptr, weight, nullptr, stream);
         src = states[k];
     }
     if (uvs) h->uv_field = nullptr;
@@ -606,7 +620,7 @@ eselbm_status eselbm_rollout_adjoints(eselbm_handle h, const void *const *states
 {
     if (!h || !states || !lam || !other) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: NULL argument");
     if (n < 1) return fail(ESELBM_E_ARG, "eselbm_rollout_adjoints: n must be >= 1");
-    // every call's arguments before the first is made
+    // every call's arguments before the first is made, and not again with it
     for (int k = 0; k < n; ++k) {
         const void *from = k % 2 ? other : lam, *to = k % 2 ? lam : other;
         const bool diss = uvs && uvs[k];
@@ -618,8 +632,9 @@ eselbm_status eselbm_rollout_adjoints(eselbm_handle h, const void *const *states
     }
     eselbm_status st = ESELBM_OK;
     for (int k = 0; k < n && st == ESELBM_OK; ++k) {
-        st = uvs && uvs[k] ? eselbm_adjoint_step_diss(h, states[k], lam, uvs[k], weight, other, tau, force_grad, stream)
-                           : eselbm_adjoint_step(h, states[k], lam, nullptr, other, tau, force_grad, stream);
+        const bool diss = uvs && uvs[k];
+        st = adjoint_run(h, states[k], lam, nullptr, diss ? uvs[k] : nullptr, diss ? weight : 0.0, other, tau, force_grad,
+                         stream, diss ? "eselbm_adjoint_step_diss" : "eselbm_adjoint_step");
         void *t = lam;
         lam = other;
         other = t;
